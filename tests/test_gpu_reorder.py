@@ -156,3 +156,33 @@ def test_reorder_full_size(name):
         got = tc.untile(np_of(w2t.qweight[t:t + 1]), w.K2, 16)
         exp = o.fold_sample(w2.qweight, eP2, None, np.arange(w.K2), np.arange(16 * t, 16 * t + 16))
         assert np.array_equal(o.unpack_rows(got), exp), t
+
+
+@pytest.mark.parametrize("K1,N1,N2,G", [
+    (20480, 40, 24, 128),     # the most rows a 16-column tile in LDS takes, ragged N
+    (20488, 40, 24, 8),       # past it: word by word
+    (136, 10248, 24, 64),     # W2: 8-column tiles (K2 > 10240), a partial last group, N2 % 16 == 8
+    (72, 40960, 8, 128),      # the widest row and the most rows the LDS passes take
+    (72, 40968, 8, 128),      # past both
+])
+@pytest.mark.parametrize("layout", ["gptq", "tiled"])
+def test_reorder_lds_limits(K1, N1, N2, G, layout):
+    """The edges of the passes through LDS (columns and rows), bit-exact."""
+    import torch
+    import paper_2402_04925_amd as tpdq
+    dev = torch_dev()
+    lay = tpdq.LAYOUT_TILED if layout == "tiled" else tpdq.LAYOUT_GPTQ
+    log(f"reorder limits K1={K1} N1={N1} N2={N2} G={G} {layout}")
+    w1, w2 = inputs.make_custom(K1, N1, N2, G, 21)
+    P1, g1, P2, g2, w1o, w2o = tpdq.reorder(layer_to_dev(w1, dev), layer_to_dev(w2, dev), layout=lay)
+    torch.cuda.synchronize()
+    eP1, eg1 = o.reorder(w1.g_idx)
+    eP2, eg2 = o.reorder(w2.g_idx)
+    f1, f2 = o.fold(_d(w1), _d(w2), eP1, eP2)
+    assert np.array_equal(np_of(P1), eP1) and np.array_equal(np_of(g1), eg1)
+    assert np.array_equal(np_of(P2), eP2) and np.array_equal(np_of(g2), eg2)
+    for got, f in ((w1o, f1), (w2o, f2)):
+        exp = tc.tile(f["qweight"]) if layout == "tiled" else f["qweight"]
+        assert np.array_equal(np_of(got.qweight), exp)
+    assert np.array_equal(np_of(w1o.scales), f1["scales"])
+    assert np.array_equal(np_of(w1o.qzeros), f1["qzeros"])
