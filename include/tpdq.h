@@ -278,8 +278,9 @@ tpdq_status tpdq_mlp_shard_noalloc(const void* X, int64_t ldx, int32_t M, const 
  * w_up must have w_gate's K, N, group size, num_groups, layout, leading
  * dimensions and zero offset (TPDQ_ERR_SHAPE otherwise); w_down->K == w_gate->N.
  * X, Y1, Y2_partial, alignment and workspace as for tpdq_mlp_shard, with
- * tpdq_workspace_bytes(3, M, w_gate, w_down). Runs the decode kernels at
- * every M (batches of more than 64 rows in launches of 64).
+ * tpdq_workspace_bytes(3, M, w_gate, w_down). On the ordered path with tiled
+ * weights, M > 64 runs the M-tiled kernel (64-row tiles, weights kept exact);
+ * every other call the decode kernels (more than 64 rows in launches of 64).
  */
 tpdq_status tpdq_gated_mlp_shard(const void* X, int64_t ldx, int32_t M, const int32_t* P1,
                                  const tpdq_w4* w_gate, const tpdq_w4* w_up, const tpdq_w4* w_down,
@@ -288,8 +289,9 @@ tpdq_status tpdq_gated_mlp_shard(const void* X, int64_t ldx, int32_t M, const in
 
 /* Workspace bytes for op 0 (tpdq_reorder: a = w1, b = w2 or NULL),
  * 1 (tpdq_w4a16_gemm: a = w), 2 (tpdq_mlp_shard: a = w1, b = w2) or
- * 3 (tpdq_gated_mlp_shard: a = w_gate, b = w_down) at batch M. Returns 0
- * when the arguments are invalid. */
+ * 3 (tpdq_gated_mlp_shard: a = w_gate, b = w_down) at batch M: what the
+ * fastest routes take. A call accepts less where a slower route of it does
+ * with less. Returns 0 when the arguments are invalid. */
 size_t tpdq_workspace_bytes(int op, int32_t M, const tpdq_w4* a, const tpdq_w4* b);
 
 /* Static description of a status code. */

@@ -104,12 +104,24 @@ size_t decode_gather_bytes(int M, int K) {
 
 size_t mtile_gather_bytes(int M, int K, bool perm) { return perm ? align_up((size_t)M * K * 2) : 0; }
 
+// The workspace a route is chosen for. A call is accepted with the bytes that
+// its base route (kBaseWs) takes; a route that takes more workspace to be
+// faster is used where the caller's buffer holds it.
+constexpr size_t kBaseWs = 0;
+constexpr size_t kAnyWs = SIZE_MAX;
+
 // The M-tiled kernel's plan when it covers the call. With a perm its row
 // gather (k_gather_rows) stages one row of X, K halves, in LDS: past that the
 // call runs through the decode kernels, whose gathers have no such limit.
-bool mtile_for(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, MtilePlan* p) {
+// What only makes a call faster than its base route (exact plans, K splits at
+// prefill sizes) is planned where `avail` bytes of workspace hold it.
+bool mtile_for(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, int dt, bool gated, size_t avail,
+               MtilePlan* p) {
   if (perm && (size_t)w->K * 2 > kLdsMax) return false;
-  return plan_mtile(M, perm ? (int64_t)w->K : ldx, w, meta, p);
+  const size_t gather = mtile_gather_bytes(M, w->K, perm);
+  const bool optional = avail != kBaseWs && avail >= gather;
+  return plan_mtile(M, perm ? (int64_t)w->K : ldx, w, meta, dt, gated, optional,
+                    optional ? avail - gather : 0, p);
 }
 
 // The decode plan of one launch of mc <= 64 rows, as run_gemm makes it: with
@@ -148,13 +160,11 @@ size_t decode_part_bytes(const DecodePlan& p, int mc, int N) {
 
 // Bytes the call (X with leading dimension ldx, optional perm) uses. Decode:
 // [prepared operand][wide kernel's partials], the partials after the
-// prepared-operand region whenever either is used. The plans, and so the
-// bytes, are the same for both element types.
-// The gated GEMM (gated = true) runs the decode kernels only.
-size_t gemm_ws_need(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, int dt = TPDQ_FP16,
-                    bool gated = false) {
+// prepared-operand region whenever either is used.
+size_t gemm_ws_need(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, int dt, bool gated,
+                    size_t avail) {
   MtilePlan p;
-  if (!gated && mtile_for(M, ldx, perm, w, meta, &p))
+  if (mtile_for(M, ldx, perm, w, meta, dt, gated, avail, &p))
     return mtile_gather_bytes(M, w->K, perm) + mtile_part_bytes(p, M, w->N);
   DecodePlan dp;
   bool prepared = false;
@@ -178,23 +188,24 @@ struct GemmIO {
   uint16_t* yp = nullptr;
   int yp_natural = 0;
   bool x_prepared = false;
-  const tpdq_w4* up = nullptr;  // gated GEMM: Y = silu(X' W) * (X' W_up), decode kernels only
+  const tpdq_w4* up = nullptr;  // gated GEMM: Y = silu(X' W) * (X' W_up)
 };
 
-// One GEMM through the decode kernels, M cut into launches of <= 64 rows.
+// One GEMM: the M-tiled kernel where it is planned (ws holds ws_bytes), else
+// the decode kernels, M cut into launches of <= 64 rows.
 // perm != NULL: the operand is X[:, perm]; it is gathered inside the kernel
 // when it fits in LDS, else into the workspace first (already in operand
 // order).
 tpdq_status run_gemm(const uint16_t* X, int64_t ldx, int M, const int32_t* perm, const tpdq_w4* w,
-                     tpdq_path path, int dt, uint16_t* Y, int64_t ldy, char* ws, hipStream_t st,
-                     const GemmIO& io = GemmIO()) {
+                     tpdq_path path, int dt, uint16_t* Y, int64_t ldy, char* ws, size_t ws_bytes,
+                     hipStream_t st, const GemmIO& io = GemmIO()) {
   const int meta = meta_mode(path);
   // sorted rows in groups of G read no g_idx; in groups of unequal sizes their
   // sorted g_idx gives each row's group (the per-row kernel, on sorted rows)
   const int32_t* gidx = path == TPDQ_PATH_ORDERED && w->group_size > 0 ? nullptr : w->g_idx;
   MtilePlan mp;
   const bool gated = io.up != nullptr;
-  if (!gated && mtile_for(M, ldx, perm != nullptr, w, meta, &mp)) {
+  if (mtile_for(M, ldx, perm != nullptr, w, meta, dt, gated, ws ? ws_bytes : kBaseWs, &mp)) {
     // M-tiled MFMA GEMM over all rows, the activations gathered first
     const uint16_t* Xa = X;
     int64_t lda = ldx;
@@ -221,6 +232,11 @@ tpdq_status run_gemm(const uint16_t* X, int64_t ldx, int M, const int32_t* perm,
     a.num_groups = w->num_groups;
     a.zoff = w->zero_offset;
     a.dt = dt;
+    if (gated) {
+      a.qw_up = (const uint32_t*)io.up->qweight;
+      a.sc_up = (const uint16_t*)io.up->scales;
+      a.qz_up = (const uint32_t*)io.up->qzeros;
+    }
     a.Y = Y;
     a.ldy = ldy;
     float* part = (float*)(ws + mtile_gather_bytes(M, w->K, perm != nullptr));
@@ -304,8 +320,8 @@ bool mlp_prepared_y1(int M, int64_t ldx, bool perm, const tpdq_w4* w1, const tpd
                      int dt, bool gated = false) {
   if (M > kDecodeMaxM || w1->N % 128 != 0) return false;
   MtilePlan mp;
-  if ((!gated && mtile_for(M, ldx, perm, w1, meta, &mp)) ||
-      plan_mtile(M, w1->N, w2, meta, &mp))
+  if (mtile_for(M, ldx, perm, w1, meta, dt, gated, kBaseWs, &mp) ||
+      mtile_for(M, w1->N, false, w2, meta, dt, false, kBaseWs, &mp))
     return false;
   DecodePlan p1, p2;
   bool prepared = false;
@@ -359,6 +375,38 @@ tpdq_status check_common(int32_t M, tpdq_path path, tpdq_dtype dtype) {
   return TPDQ_OK;
 }
 
+// The most workspace any call of this shape uses on the routes chosen for
+// `avail` bytes (kBaseWs: what a call must bring; kAnyWs: what the fastest
+// routes take).
+size_t ws_bound(int op, int32_t M, const tpdq_w4* a, const tpdq_w4* b, size_t avail) {
+  if (!a || a->K <= 0 || a->N <= 0 || a->group_size < 0 || a->num_groups <= 0) return 0;
+  if (op == 0) {
+    size_t n = 256 + align_up((size_t)a->num_groups * 4);
+    if (b) n += align_up((size_t)b->num_groups * 4);
+    return n;
+  }
+  if (M < 1) return 0;
+  // the leading dimension of X is not known here; ldx = K is the case that can
+  // take the M-tiled kernel
+  auto gemm_max = [&](const tpdq_w4* w, bool perm_possible, bool gated) {
+    size_t n = perm_possible ? decode_gather_bytes(M, w->K) : 0;
+    for (int pm = 0; pm <= (perm_possible ? 1 : 0); ++pm)
+      for (int meta : {kMetaGroup, kMetaRowLds, kMetaRowGlobal})
+        for (int dt : {TPDQ_FP16, TPDQ_BF16})
+          n = std::max(n, gemm_ws_need(M, w->K, pm == 1, w, meta, dt, gated, avail));
+    return n;
+  };
+  if (op == 1) return gemm_max(a, true, false);
+  if (op == 2 || op == 3) {
+    if (!b) return 0;
+    // GEMM1's region, then Y1 in GEMM2's operand order (mlp_prepared_y1);
+    // op 3: GEMM1 is the gated GEMM (a = w_gate)
+    const size_t y1p = M <= kDecodeMaxM ? decode_gather_bytes(M, a->N) : 0;
+    return std::max(gemm_max(a, true, op == 3) + y1p, gemm_max(b, false, false));
+  }
+  return 0;
+}
+
 }  // namespace
 
 extern "C" {
@@ -382,38 +430,7 @@ const char* tpdq_status_string(tpdq_status s) {
 const char* tpdq_last_error(void) { return g_last_error.c_str(); }
 
 size_t tpdq_workspace_bytes(int op, int32_t M, const tpdq_w4* a, const tpdq_w4* b) {
-  if (!a || a->K <= 0 || a->N <= 0 || a->group_size < 0 || a->num_groups <= 0) return 0;
-  if (op == 0) {
-    size_t n = 256 + align_up((size_t)a->num_groups * 4);
-    if (b) n += align_up((size_t)b->num_groups * 4);
-    return n;
-  }
-  if (M < 1) return 0;
-  // the most any call of this shape can use (the leading dimension of X is
-  // not known here; ldx = K is the case that can take the M-tiled kernel)
-  auto gemm_max = [&](const tpdq_w4* w, bool perm_possible) {
-    size_t n = perm_possible ? decode_gather_bytes(M, w->K) : 0;
-    for (int pm = 0; pm <= (perm_possible ? 1 : 0); ++pm)
-      for (int meta : {kMetaGroup, kMetaRowLds, kMetaRowGlobal})
-        n = std::max(n, gemm_ws_need(M, w->K, pm == 1, w, meta));
-    return n;
-  };
-  if (op == 1) return gemm_max(a, true);
-  if (op == 2 || op == 3) {
-    if (!b) return 0;
-    // GEMM1's region, then Y1 in GEMM2's operand order (mlp_prepared_y1);
-    // op 3: GEMM1 is the gated GEMM (a = w_gate)
-    const size_t y1p = M <= kDecodeMaxM ? decode_gather_bytes(M, a->N) : 0;
-    size_t g1 = gemm_max(a, true);
-    if (op == 3) {
-      g1 = decode_gather_bytes(M, a->K);
-      for (int pm = 0; pm <= 1; ++pm)
-        for (int meta : {kMetaGroup, kMetaRowLds, kMetaRowGlobal})
-          g1 = std::max(g1, gemm_ws_need(M, a->K, pm == 1, a, meta, TPDQ_FP16, true));
-    }
-    return std::max(g1 + y1p, gemm_max(b, false));
-  }
-  return 0;
+  return std::max(ws_bound(op, M, a, b, kBaseWs), ws_bound(op, M, a, b, kAnyWs));
 }
 
 tpdq_status tpdq_reorder(const tpdq_w4* w1, const tpdq_w4* w2, int32_t* P1, int32_t* g1_sorted,
@@ -535,16 +552,17 @@ tpdq_status tpdq_w4a16_gemm(const void* X, int64_t ldx, int32_t M, const int32_t
   if (!aligned(X, 16) || ldx % 8)
     return fail(TPDQ_ERR_ALIGN, "X needs 16-byte alignment and ldx %% 8 == 0");
   if (!aligned(Y, 8) || ldy % 4) return fail(TPDQ_ERR_ALIGN, "Y needs 8-byte alignment, ldy %% 4 == 0");
-  // a call that uses a workspace (a gather always does) takes the documented
-  // tpdq_workspace_bytes(1, ...), an upper bound of what it uses
-  const size_t bound = tpdq_workspace_bytes(1, M, w, nullptr);
-  const size_t need = gemm_ws_need(M, ldx, x_perm != nullptr, w, meta_mode(path), dtype);
+  // a call whose base route uses a workspace (a gather always does) takes an
+  // upper bound of what any route of this shape does
+  const size_t bound = ws_bound(1, M, w, nullptr, kBaseWs);
+  const size_t need =
+      gemm_ws_need(M, ldx, x_perm != nullptr, w, meta_mode(path), dtype, false, kBaseWs);
   if ((x_perm || need) && (!workspace || ws_bytes < bound))
     return fail(TPDQ_ERR_WORKSPACE, "GEMM needs %zu workspace bytes, got %zu", bound, ws_bytes);
   if (workspace && !aligned(workspace, 16))
     return fail(TPDQ_ERR_ALIGN, "workspace needs 16-byte alignment");
   return run_gemm((const uint16_t*)X, ldx, M, x_perm, w, path, dtype, (uint16_t*)Y, ldy,
-                  (char*)workspace, (hipStream_t)stream);
+                  (char*)workspace, ws_bytes, (hipStream_t)stream);
 }
 
 }  // extern "C"
@@ -575,9 +593,9 @@ tpdq_status mlp_shard(const void* X, int64_t ldx, int32_t M, const int32_t* P1, 
   if (!aligned(Y1, 16) || !aligned(Y2_partial, 8))
     return fail(TPDQ_ERR_ALIGN, "Y1 needs 16-byte and Y2_partial 8-byte alignment");
   const int meta = meta_mode(path);
-  const size_t bound = tpdq_workspace_bytes(2, M, w1, w2);
-  const size_t need = std::max(gemm_ws_need(M, ldx, !act, w1, meta, dtype),
-                               gemm_ws_need(M, w1->N, false, w2, meta, dtype));
+  const size_t bound = ws_bound(2, M, w1, w2, kBaseWs);
+  const size_t need = std::max(gemm_ws_need(M, ldx, !act, w1, meta, dtype, false, kBaseWs),
+                               gemm_ws_need(M, w1->N, false, w2, meta, dtype, false, kBaseWs));
   if (noalloc) {
     if (bound > kScratchBytes)
       return fail(TPDQ_ERR_WORKSPACE,
@@ -596,19 +614,19 @@ tpdq_status mlp_shard(const void* X, int64_t ldx, int32_t M, const int32_t* P1, 
   char* ws = (char*)workspace;
   GemmIO io1, io2;
   if (workspace && ws_bytes >= bound && mlp_prepared_y1(M, ldx, !act, w1, w2, meta, dtype)) {
-    const size_t off = gemm_ws_need(M, ldx, !act, w1, meta, dtype);
+    const size_t off = gemm_ws_need(M, ldx, !act, w1, meta, dtype, false, kBaseWs);
     io1.yp = (uint16_t*)(ws + off);
     io1.yp_natural = w2->layout == TPDQ_LAYOUT_TILED ? 1 : 0;
     io2.x_prepared = true;
   }
   st = run_gemm((const uint16_t*)X, ldx, M, act ? nullptr : P1, w1, path, dtype, (uint16_t*)Y1, w1->N,
-                ws, s, io1);
+                ws, ws_bytes, s, io1);
   if (st != TPDQ_OK) return st;
   if (io2.x_prepared)
-    return run_gemm(io1.yp, w1->N, M, nullptr, w2, path, dtype, (uint16_t*)Y2_partial, w2->N, ws, s,
-                    io2);
+    return run_gemm(io1.yp, w1->N, M, nullptr, w2, path, dtype, (uint16_t*)Y2_partial, w2->N, ws, ws_bytes,
+                    s, io2);
   return run_gemm((const uint16_t*)Y1, w1->N, M, nullptr, w2, path, dtype, (uint16_t*)Y2_partial,
-                  w2->N, ws, s);
+                  w2->N, ws, ws_bytes, s);
 }
 
 }  // namespace
@@ -659,9 +677,9 @@ tpdq_status tpdq_gated_mlp_shard(const void* X, int64_t ldx, int32_t M, const in
   if (!aligned(Y1, 16) || !aligned(Y2_partial, 8))
     return fail(TPDQ_ERR_ALIGN, "Y1 needs 16-byte and Y2_partial 8-byte alignment");
   const int meta = meta_mode(path);
-  const size_t bound = tpdq_workspace_bytes(3, M, w_gate, w_down);
-  const size_t need = std::max(gemm_ws_need(M, ldx, !act, w_gate, meta, dtype, true),
-                               gemm_ws_need(M, w_gate->N, false, w_down, meta, dtype));
+  const size_t bound = ws_bound(3, M, w_gate, w_down, kBaseWs);
+  const size_t need = std::max(gemm_ws_need(M, ldx, !act, w_gate, meta, dtype, true, kBaseWs),
+                               gemm_ws_need(M, w_gate->N, false, w_down, meta, dtype, false, kBaseWs));
   if ((!act || need) && (!workspace || ws_bytes < bound))
     return fail(TPDQ_ERR_WORKSPACE, "gated MLP needs %zu workspace bytes, got %zu", bound, ws_bytes);
   if (workspace && !aligned(workspace, 16))
@@ -672,18 +690,18 @@ tpdq_status tpdq_gated_mlp_shard(const void* X, int64_t ldx, int32_t M, const in
   GemmIO io1, io2;
   io1.up = w_up;
   if (workspace && ws_bytes >= bound && mlp_prepared_y1(M, ldx, !act, w_gate, w_down, meta, dtype, true)) {
-    io1.yp = (uint16_t*)(ws + gemm_ws_need(M, ldx, !act, w_gate, meta, dtype, true));
+    io1.yp = (uint16_t*)(ws + gemm_ws_need(M, ldx, !act, w_gate, meta, dtype, true, kBaseWs));
     io1.yp_natural = w_down->layout == TPDQ_LAYOUT_TILED ? 1 : 0;
     io2.x_prepared = true;
   }
   st = run_gemm((const uint16_t*)X, ldx, M, act ? nullptr : P1, w_gate, path, dtype, (uint16_t*)Y1,
-                w_gate->N, ws, s, io1);
+                w_gate->N, ws, ws_bytes, s, io1);
   if (st != TPDQ_OK) return st;
   if (io2.x_prepared)
     return run_gemm(io1.yp, w_gate->N, M, nullptr, w_down, path, dtype, (uint16_t*)Y2_partial,
-                    w_down->N, ws, s, io2);
+                    w_down->N, ws, ws_bytes, s, io2);
   return run_gemm((const uint16_t*)Y1, w_gate->N, M, nullptr, w_down, path, dtype,
-                  (uint16_t*)Y2_partial, w_down->N, ws, s);
+                  (uint16_t*)Y2_partial, w_down->N, ws, ws_bytes, s);
 }
 
 }  // extern "C"

@@ -348,7 +348,7 @@ __device__ __forceinline__ void reduce_store(const GemmArgs& a, f4_t (&acc)[MT][
       const int row = t * kTileM + 4 * (ln >> 4) + e;
       const int c = n0 + (ln & 15);
       if (row < a.M && c < a.N) {
-        const uint16_t v = float_to_bits<DT>(g / (1.f + __expf(-g)) * u);  // silu(g) * u
+        const uint16_t v = float_to_bits<DT>(silu_mul(g, u));
         a.Y[(int64_t)row * a.ldy + c] = v;
         if (a.Yp) a.Yp[prepared_offset(row, c, a.N >> 5, a.yp_natural)] = v;
       }

@@ -228,7 +228,7 @@ hipError_t launch_decode(const GemmArgs& a0, const DecodePlan& p, float* part, h
     hipLaunchKernelGGL(k, dim3(wgs * p.ks), dim3(kWideWaves * 64), p.lds_bytes, s, a);
     e = hipGetLastError();
     if (e != hipSuccess || p.ks == 1) return e;
-    return launch_splitk_reduce(part, p.ks, a.M, a.N, a.Y, a.ldy, p.dt, s);
+    return launch_splitk_reduce(part, p.ks, a.M, a.N, a.Y, a.ldy, p.dt, false, s);
   }
   DecodeKernel k = decode_kernel(p);
   if (!k) return hipErrorInvalidValue;

@@ -24,10 +24,12 @@
 // of block b (the most recent ones), and the barrier then makes every wave's
 // LDS writes visible.
 // Dequantizing to fp16 before the MFMA rounds each weight once (relative
-// error 2^-12); the decode kernels keep q - z exact and scale in fp32, but
-// here that would double the accumulator registers and the VALU work per
-// MFMA. With bf16 activations the weight is formed in fp32 and rounded once
-// to bf16 (relative error 2^-9), about four times the VALU work of fp16.
+// error 2^-12). With bf16 activations the weight is formed in fp32 and rounded
+// once to bf16 (relative error 2^-9), about four times the VALU work of fp16.
+// The exact variants (see k_prefill) keep q - z in the MFMAs and scale in fp32
+// as the decode kernels do, on 64-row tiles: they serve what would otherwise
+// run in decode launches of 64 rows. Gated Llama-70B TP=8 MLP at M = 1000,
+// bf16: 514 -> 222 us (gate and up in one launch at 0.9 PFLOP/s).
 #include "kernels_common.h"
 
 #include <algorithm>
@@ -37,12 +39,14 @@ namespace {
 
 constexpr int kPWT = 4;    // column tiles per wave
 constexpr int kPWwave = kPWT * 64 * 16;
-constexpr int kPMwave = 3 * 256;
+// metadata records of 256 bytes per wave and block: two of scales and one of
+// zeros (64 columns), or gated one of each for 32 columns of gate and of up
+__host__ __device__ constexpr int pf_meta(bool gated) { return (gated ? 4 : 3) * 256; }
 // LDS per stage with RT row tiles and NW waves: activations
 // [RT row tiles][4 steps][64 lanes] x 16 B, then per wave its weights
-// [4 tiles][64 lanes] x 16 B and its metadata (three 256-byte records)
-__host__ __device__ constexpr int pf_stage(int rt, int nw) {
-  return rt * 4 * 64 * 16 + nw * (kPWwave + kPMwave);
+// [4 tiles][64 lanes] x 16 B and its metadata
+__host__ __device__ constexpr int pf_stage(int rt, int nw, bool gated) {
+  return rt * 4 * 64 * 16 + nw * (kPWwave + pf_meta(gated));
 }
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
@@ -86,20 +90,39 @@ __device__ __forceinline__ u4_t dequant_scaled_bf16(const UnpackConsts<kBF16>& k
 // Two waves per SIMD (the 8-wave workgroup, or two 4-wave workgroups per CU):
 // 256 registers per lane, with the accumulators in the architectural VGPRs
 // (no accumulator copies between loop iterations).
-template <int SPG, int NW, int ST, int RT, int DT>
+//
+// EXACT: the MFMAs take q - z (bf16: 128 + q), exact in the element type, into
+// a second set of accumulators, and every group closes with its scale in fp32
+// (bf16: and its zero, against the group's sum of X from one more MFMA per row
+// tile), as the decode kernels do: no weight is rounded. Twice the
+// accumulators, so RT = 4; per MFMA 9 / 4 VALU of unpacking and, at G = 128,
+// one of scaling (bf16 two).
+// GATED (EXACT): Y = silu(X W) * (X W_up). A wave's four column tiles are 32
+// columns of gate (tiles 0, 1) and the same 32 of up (tiles 2, 3), so that the
+// epilogue has both products of an element in one lane; split partials are
+// [split][gate, up][M][N].
+template <int SPG, int NW, int ST, int RT, int DT, bool EXACT = false, bool GATED = false>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_prefill(GemmArgs a) {
+  static_assert(!EXACT || RT <= 4, "two accumulators per output");
+  static_assert(!GATED || EXACT, "the gated product keeps its weights exact");
   // groups per 128-row block: G = 32, 64, 128 -> 4, 2, 1; G = 256 -> one
   // group spans two blocks (each block loads it)
   constexpr int GPK = SPG >= 4 ? 1 : 4 / SPG;
-  constexpr int NSD = (GPK + 1) / 2;  // scale records per wave and block
+  // scale records per wave and block (two groups of 64 columns in each;
+  // gated: four groups of 32 columns, one record for gate, one for up)
+  constexpr int NSD = GATED ? 2 : (GPK + 1) / 2;
+  constexpr int NZ = GATED ? 2 : 1;
+  constexpr int CWAVE = GATED ? 32 : 64;  // output columns per wave
   static_assert((RT * 4) % NW == 0, "activation records split evenly over the waves");
   constexpr int AREC = RT * 4 / NW;   // activation records per wave and block
   // loads per wave and block: activations, scales, zeros, weights
-  constexpr int LPB = AREC + NSD + 1 + kPWT;
-  constexpr int STAGE = pf_stage(RT, NW);
+  constexpr int LPB = AREC + NSD + NZ + kPWT;
+  constexpr int STAGE = pf_stage(RT, NW, GATED);
+  constexpr int MWAVE = pf_meta(GATED);
+  constexpr int ZOFF = 512;  // the zeros behind the scales in a wave's metadata
   constexpr int ABYTES = RT * 4 * 64 * 16;
   constexpr int BM = 16 * RT;
-  constexpr int BN = 64 * NW;
+  constexpr int BN = CWAVE * NW;
   extern __shared__ __align__(16) unsigned char smem[];
 
   const int tid = threadIdx.x;
@@ -119,7 +142,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   const int bm = tl - bn * nbm;
   const int row0 = bm * BM;
   const int col0 = bn * BN;
-  const int cw = col0 + 64 * wave;
+  const int cw = col0 + CWAVE * wave;
   const int nblk_all = (a.K + 127) >> 7;
   // this workgroup's blocks [kb0, kb1)
   const int kb0 = (int)((int64_t)nblk_all * kidx / ks);
@@ -135,13 +158,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   // columns 128 b + 32 u + 8 (l / 16) .. +7
   const uint32_t x_lane = ((uint32_t)j * (uint32_t)a.ldx + 8u * (uint32_t)kq) * 2u;
   const uint32_t x_rt = 16u * (uint32_t)a.ldx * 2u;
-  // scales: record d, lane l = group 2 d + l / 32, columns 2 (l % 32), +1
-  const uint32_t s_lane = (uint32_t)(lane >> 5) * (uint32_t)a.lds * 2u +
-                          ((uint32_t)cw + 2u * (uint32_t)(lane & 31)) * 2u;
-  const uint32_t z_lane =
-      ((uint32_t)(lane >> 3) * (uint32_t)a.ldz + (uint32_t)(cw >> 3) + (uint32_t)(lane & 7)) * 4u;
-  // zeros: lane l = group l / 8, word l % 8 of the wave's 8
-  const bool z_used = (lane >> 3) < GPK;
+  // scales: record d, lane l = group 2 d + l / 32, columns 2 (l % 32), +1;
+  // gated: record of gate or up, lane l = group l / 16, columns 2 (l % 16), +1
+  const int sg = GATED ? lane >> 4 : lane >> 5, scol = 2 * (GATED ? lane & 15 : lane & 31);
+  const uint32_t s_lane = (uint32_t)sg * (uint32_t)a.lds * 2u + (uint32_t)(cw + scol) * 2u;
+  // zeros: lane l = group l / 8, word l % 8 of the wave's 8 (gated l / 4, l % 4)
+  const int zg = GATED ? lane >> 2 : lane >> 3, zw0 = GATED ? lane & 3 : lane & 7;
+  const uint32_t z_lane = ((uint32_t)zg * (uint32_t)a.ldz + (uint32_t)((cw >> 3) + zw0)) * 4u;
+  const bool z_used = zg < GPK;
   // weights: tile (cw / 16 + i), block b: lane l's 16 bytes
   const uint32_t w_lane = ((uint32_t)(cw >> 4) * (uint32_t)a.ldq + 4u * (uint32_t)lane) * 4u;
   const uint32_t w_tile = (uint32_t)a.ldq * 4u;
@@ -163,10 +187,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   }
 #pragma unroll
   for (int d = 0; d < NSD; ++d)
-    offS[d] = 2 * d + (lane >> 5) < GPK ? s_lane + (uint32_t)(2 * d) * (uint32_t)a.lds * 2u : kOutOfRange;
+    offS[d] = GATED ? (sg < GPK ? s_lane : kOutOfRange)
+                    : (2 * d + sg < GPK ? s_lane + (uint32_t)(2 * d) * (uint32_t)a.lds * 2u : kOutOfRange);
   const uint32_t offZ = z_used ? z_lane : kOutOfRange;
 #pragma unroll
-  for (int i = 0; i < kPWT; ++i) offW[i] = w_lane + (uint32_t)i * w_tile;
+  for (int i = 0; i < kPWT; ++i) offW[i] = w_lane + (uint32_t)(GATED ? i & 1 : i) * w_tile;
   const uint32_t xbytes = (uint32_t)(a.M - row0) * (uint32_t)a.ldx * 2u;
   const uint32_t wbytes = (uint32_t)ntiles * (uint32_t)a.ldq * 4u;
 
@@ -174,7 +199,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   // one load (the wait counts rely on it)
   auto dma_item = [&](int b, int st, int k) {
     unsigned char* sb = smem + st * STAGE;
-    unsigned char* wb = sb + ABYTES + wave * (kPWwave + kPMwave);
+    unsigned char* wb = sb + ABYTES + wave * (kPWwave + MWAVE);
     unsigned char* mb = wb + kPWwave;
     const int g0 = (128 * b) / (32 * SPG);
     const bool bok = b < kb1;
@@ -185,16 +210,20 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
       dma_to_lds<16>(r, sb + rec * 1024, b == bl ? offAt[k] : offA[k]);
     } else if (k < AREC + NSD) {
       const int d = k - AREC;
-      const __amdgpu_buffer_rsrc_t r = buffer_rsrc(a.sc + (int64_t)g0 * a.lds,
+      const uint16_t* sc = GATED && d == 1 ? a.sc_up : a.sc;
+      const __amdgpu_buffer_rsrc_t r = buffer_rsrc(sc + (int64_t)g0 * a.lds,
                                                    bok ? (uint32_t)(ng - g0) * (uint32_t)a.lds * 2u : 0u);
       dma_to_lds<4>(r, mb + d * 256, offS[d]);
-    } else if (k == AREC + NSD) {
-      const __amdgpu_buffer_rsrc_t r = buffer_rsrc(a.qz + (int64_t)g0 * a.ldz,
+    } else if (k < AREC + NSD + NZ) {
+      const int d = k - AREC - NSD;
+      const uint32_t* qz = GATED && d == 1 ? a.qz_up : a.qz;
+      const __amdgpu_buffer_rsrc_t r = buffer_rsrc(qz + (int64_t)g0 * a.ldz,
                                                    bok ? (uint32_t)(ng - g0) * (uint32_t)a.ldz * 4u : 0u);
-      dma_to_lds<4>(r, mb + 512, offZ);
+      dma_to_lds<4>(r, mb + ZOFF + d * 256, offZ);
     } else {
-      const int i = k - AREC - NSD - 1;
-      const __amdgpu_buffer_rsrc_t r = buffer_rsrc(a.qw + (int64_t)256 * b,
+      const int i = k - AREC - NSD - NZ;
+      const uint32_t* qw = GATED && i >= 2 ? a.qw_up : a.qw;
+      const __amdgpu_buffer_rsrc_t r = buffer_rsrc(qw + (int64_t)256 * b,
                                                    bok ? wbytes - 1024u * (uint32_t)b : 0u);
       dma_to_lds<16>(r, wb + i * 1024, offW[i]);
     }
@@ -209,32 +238,50 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   for (int r = 0; r < RT; ++r)
 #pragma unroll
     for (int i = 0; i < kPWT; ++i) acc[r][i] = f4_t{0.f, 0.f, 0.f, 0.f};
+  f4_t gacc[EXACT ? RT : 1][EXACT ? kPWT : 1];   // EXACT: the open group
+  f4_t xsum[EXACT && DT == kBF16 ? RT : 1];
+  const f4_t fz = {0.f, 0.f, 0.f, 0.f};
+  const u4_t ones = {kBf16OnePair, kBf16OnePair, kBf16OnePair, kBf16OnePair};
+  float sf[kPWT], zs[kPWT];  // bf16: the open group's scale and zero term
+  uint32_t z1024[kPWT], z64[kPWT], s2[kPWT];
 
   // block in stage st; the loads of block bn go out one after each column
   // tile's MFMAs, into stage sn
-  auto compute = [&](int st, int bnext, int sn) {
+  auto compute = [&](int b, int st, int bnext, int sn) {
     const u4_t* ab = (const u4_t*)(smem + st * STAGE);
-    const u4_t* wb = (const u4_t*)(smem + st * STAGE + ABYTES + wave * (kPWwave + kPMwave));
+    const u4_t* wb = (const u4_t*)(smem + st * STAGE + ABYTES + wave * (kPWwave + MWAVE));
     const unsigned char* mb = (const unsigned char*)wb + kPWwave;
     u4_t w[kPWT];
 #pragma unroll
     for (int i = 0; i < kPWT; ++i) w[i] = wb[i * 64 + lane];
-    uint32_t z1024[kPWT], z64[kPWT], s2[kPWT];
-    float sf[kPWT], zs[kPWT];  // bf16
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const bool open = SPG >= 4 ? u == 0 : (u % SPG) == 0;
+      // the MFMAs' first step of a group, and its last (G = 256: a group is
+      // blocks 2g and 2g + 1, cut where the workgroup's range is)
+      const bool first = SPG <= 4 ? open : u == 0 && ((b & 1) == 0 || b == kb0);
+      const bool last = SPG <= 4 ? (u % (SPG <= 4 ? SPG : 4)) == (SPG <= 4 ? SPG : 4) - 1
+                                 : u == 3 && ((b & 1) == 1 || b == kb1 - 1);
+      const int gi = SPG >= 4 ? 0 : u / SPG;
+      // scale bits and zero code of column j of tile i in this block's group
+      auto meta_of = [&](int i, uint32_t& sv, uint32_t& zc) {
+        const int c = 16 * (GATED ? i & 1 : i) + j;
+        const int ms = GATED ? (i >> 1) * 256 + gi * 64 : gi * 128;  // record and group
+        const int mz = ZOFF + (GATED ? (i >> 1) * 256 + gi * 16 : gi * 32);
+        sv = *(const uint16_t*)(mb + ms + 2 * c);
+        const uint32_t zw = *(const uint32_t*)(mb + mz + 4 * (c >> 3));
+        zc = ((zw >> (4 * (c & 7))) & 0xFu) + (uint32_t)a.zoff;  // up to 16
+      };
       if (open) {
-        const int gi = SPG >= 4 ? 0 : u / SPG;
 #pragma unroll
         for (int i = 0; i < kPWT; ++i) {
-          const int c = 16 * i + j;
-          const uint32_t sv = *(const uint16_t*)(mb + gi * 128 + 2 * c);
-          const uint32_t zw = *(const uint32_t*)(mb + 512 + gi * 32 + 4 * (c >> 3));
-          const uint32_t zc = ((zw >> (4 * (c & 7))) & 0xFu) + (uint32_t)a.zoff;  // up to 16
+          uint32_t sv, zc;
+          meta_of(i, sv, zc);
           if constexpr (DT == kBF16) {
-            sf[i] = bits_to_float<kBF16>(sv);
-            zs[i] = (128.f + (float)zc) * sf[i];
+            if constexpr (!EXACT) {
+              sf[i] = bits_to_float<kBF16>(sv);
+              zs[i] = (128.f + (float)zc) * sf[i];
+            }
           } else {
             z1024[i] = (0x6400u | zc) * 0x10001u;
             z64[i] = (0x5400u | (zc << 4)) * 0x10001u;
@@ -248,13 +295,44 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
       for (int i = 0; i < kPWT; ++i) {
         u4_t bv;
-        if constexpr (DT == kBF16)
+        if constexpr (EXACT)
+          bv = unpack_step<DT>(kc, w[i][u], z1024[i], z64[i]);
+        else if constexpr (DT == kBF16)
           bv = dequant_scaled_bf16(kc, w[i][u], sf[i], zs[i]);
         else
           bv = dequant_scaled(kc, w[i][u], z1024[i], z64[i], s2[i]);
 #pragma unroll
-        for (int r = 0; r < RT; ++r) acc[r][i] = mfma_k32<DT>(av[r], bv, acc[r][i]);
+        for (int r = 0; r < RT; ++r) {
+          if constexpr (EXACT)
+            gacc[r][i] = mfma_k32<DT>(av[r], bv, first ? fz : gacc[r][i]);
+          else
+            acc[r][i] = mfma_k32<DT>(av[r], bv, acc[r][i]);
+        }
         if (4 * u + i < LPB) dma_item(bnext, sn, 4 * u + i);
+      }
+      if constexpr (EXACT) {
+        if constexpr (DT == kBF16) {
+#pragma unroll
+          for (int r = 0; r < RT; ++r) xsum[r] = mfma_k32<DT>(av[r], ones, first ? fz : xsum[r]);
+        }
+        if (last) {
+          // the group's scale (and zero) are read again here: held since the
+          // group's first step they would cost registers the kernel has not
+#pragma unroll
+          for (int i = 0; i < kPWT; ++i) {
+            uint32_t sv, zc;
+            meta_of(i, sv, zc);
+            const float sc = bits_to_float<DT>(sv);
+            const float zt = 128.f + (float)zc;
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {
+              if constexpr (DT == kBF16)
+                acc[r][i] += sc * (gacc[r][i] - zt * xsum[r]);
+              else
+                acc[r][i] += sc * gacc[r][i];
+            }
+          }
+        }
       }
     }
   };
@@ -276,7 +354,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   for (int b = kb0; b < kb1; ++b) {
     sync();
     const int sn = st == 0 ? ST - 1 : st - 1;
-    compute(st, b + ST - 1, sn);
+    compute(b, st, b + ST - 1, sn);
     st = st == ST - 1 ? 0 : st + 1;
   }
   // the loads past the last block (zeros) still write LDS: let them land
@@ -284,20 +362,25 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 
   // epilogue: acc[r][i] of lane (j, kq) holds rows 4 kq .. +3 of row tile r,
   // column j of the wave's tile i
-  float* part = a.part + (size_t)kidx * a.M * a.N;
+  const size_t plane = (size_t)a.M * a.N;
+  float* part = a.part + (size_t)kidx * (GATED ? 2 : 1) * plane;
 #pragma unroll
   for (int r = 0; r < RT; ++r)
 #pragma unroll
-    for (int i = 0; i < kPWT; ++i) {
+    for (int i = 0; i < (GATED ? 2 : kPWT); ++i) {
       const int c = cw + 16 * i + j;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int row = row0 + 16 * r + 4 * kq + e;
         if (row < a.M && c < a.N) {
-          if (ks > 1)
+          if (ks > 1) {
             part[(int64_t)row * a.N + c] = acc[r][i][e];
-          else
+            if constexpr (GATED) part[plane + (int64_t)row * a.N + c] = acc[r][i + 2][e];
+          } else if constexpr (GATED) {
+            a.Y[(int64_t)row * a.ldy + c] = float_to_bits<DT>(silu_mul(acc[r][i][e], acc[r][i + 2][e]));
+          } else {
             a.Y[(int64_t)row * a.ldy + c] = float_to_bits<DT>(acc[r][i][e]);
+          }
         }
       }
     }
@@ -307,10 +390,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 // 0, 1, ... (the result does not depend on which split finished first). Four
 // columns per thread: one 16-byte load per split, one 8-byte store (N % 4 ==
 // 0 and 16-byte aligned rows; otherwise one column per thread).
-template <int DT>
+// GATED: the partials are [s][gate, up][M][N] and Y = silu(gate) * up.
+template <int DT, bool GATED>
 __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__ part, int ks, int M,
                                                        int N, uint16_t* __restrict__ Y, int64_t ldy) {
   const int64_t plane = (int64_t)M * N;
+  const int64_t step = GATED ? 2 * plane : plane;
   if ((N & 3) == 0 && (ldy & 3) == 0) {
     const int n4 = N >> 2;
     const int64_t total = (int64_t)M * n4;
@@ -320,7 +405,14 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__
       const int c0 = (int)(i - (int64_t)m * n4) * 4;
       const float* src = part + (int64_t)m * N + c0;
       f4_t v = *(const f4_t*)src;
-      for (int s = 1; s < ks; ++s) v += *(const f4_t*)(src + s * plane);
+      for (int s = 1; s < ks; ++s) v += *(const f4_t*)(src + s * step);
+      if constexpr (GATED) {
+        src += plane;
+        f4_t u = *(const f4_t*)src;
+        for (int s = 1; s < ks; ++s) u += *(const f4_t*)(src + s * step);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = silu_mul(v[e], u[e]);
+      }
       const uint32_t lo = pack2<DT>(v[0], v[1]);
       const uint32_t hi = pack2<DT>(v[2], v[3]);
       *(uint2*)(Y + (int64_t)m * ldy + c0) = make_uint2(lo, hi);
@@ -332,7 +424,12 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__
     const int m = (int)(i / N);
     const int c = (int)(i - (int64_t)m * N);
     float v = part[i];
-    for (int s = 1; s < ks; ++s) v += part[s * plane + i];
+    for (int s = 1; s < ks; ++s) v += part[s * step + i];
+    if constexpr (GATED) {
+      float u = part[plane + i];
+      for (int s = 1; s < ks; ++s) u += part[s * step + plane + i];
+      v = silu_mul(v, u);
+    }
     Y[(int64_t)m * ldy + c] = float_to_bits<DT>(v);
   }
 }
@@ -364,7 +461,23 @@ __global__ __launch_bounds__(256) void k_gather_rows(const uint16_t* __restrict_
 
 }  // namespace
 
-bool plan_mtile(int M, int64_t ldx, const tpdq_w4* w, int meta, MtilePlan* p) {
+// Microseconds of one M-tiled launch by shape: workgroups run in rounds of one
+// per CU, each over nblk / ks blocks of 128 rows; split partials are written
+// once and read once by the reduce. Per block and round, measured on 6144 x
+// 6144, 8192 x 3584 and 3584 x 8192 at M = 300 to 1500: 128 x 512 tiles 2.8 us
+// (bf16 3.2), 64 x 512 tiles 1.9 us (bf16 2.5 rounded, 2.9 exact), about 4 us
+// of prologue and epilogue; partials at 4.5 TB/s plus a 4 us launch.
+static double mtile_cost(int M, int N, int nblk, int rt, int ks, bool gated, bool exact, int dt) {
+  const int bn = gated ? 256 : 512;
+  const int64_t wgs = (int64_t)((M + 16 * rt - 1) / (16 * rt)) * ((N + bn - 1) / bn) * ks;
+  const double tb = dt == kBF16 ? (rt == 8 ? 3.2 : (exact ? 2.9 : 2.5)) : (rt == 8 ? 2.8 : 1.9);
+  const double rounds = (double)((wgs + kMtileSlots - 1) / kMtileSlots);
+  const double part = ks > 1 ? 4.0 + (double)ks * M * N * (gated ? 16.0 : 8.0) / 4.5e6 : 0.0;
+  return rounds * (4.0 + tb * ((nblk + ks - 1) / ks)) + part;
+}
+
+bool plan_mtile(int M, int64_t ldx, const tpdq_w4* w, int meta, int dt, bool gated, bool optional,
+                size_t part_budget, MtilePlan* p) {
   if (meta != kMetaGroup || w->layout != TPDQ_LAYOUT_TILED) return false;
   const int K = w->K, N = w->N, G = w->group_size;
   if (M < kMtileMinM || K % 8 != 0 || G <= 0 || G % 32 != 0) return false;
@@ -380,58 +493,90 @@ bool plan_mtile(int M, int64_t ldx, const tpdq_w4* w, int meta, MtilePlan* p) {
         (int64_t)w->num_groups * w->ld_s * 2 < lim && (int64_t)w->num_groups * w->ld_z * 4 < lim))
     return false;
   MtilePlan q{};
-  if (M >= kPrefillMinM) {
-    // a dense contraction: 8 waves (two per SIMD) over 128 x 512 tiles
-    q.rt = 8;
-    q.nw = 8;
-    q.st = 2;
-    q.ks = 1;
-  } else {
-    // below prefill sizes the weight stream bounds the product; worth it
-    // only when the weights are large enough that the decode kernels'
-    // per-workgroup re-reads of X dominate: 64 x 512 tiles, 8 waves (two per
-    // SIMD, one workgroup per CU), K split as far as the workgroups still
-    // fit the kMtileSlots CUs in one round. Llama-70B TP=1 at M = 64 (MLP):
-    // 109.5 us with 64 x 256 tiles of 4 waves in 512 slots (two per CU),
-    // 106.3 us here (GEMM2 52.4 -> 48.9 us: 8 waves share one copy of the
-    // activations); more splits than fit one round are slower (8 waves in
-    // 320 slots: GEMM1 280 workgroups, 144 us), and so is one wave per SIMD
-    if ((int64_t)K * N < kMtileMinWeights) return false;
+  q.nw = 8;
+  q.st = 2;
+  q.ks = 1;
+  q.gated = gated;
+  const int nblk = (K + 127) / 128;
+  const bool big = !gated && (int64_t)K * N >= kMtileMinWeights;
+  if (big && M < kPrefillMinM) {
+    // 64 x 512 tiles, 8 waves (two per SIMD, one workgroup per CU), K split as
+    // far as the workgroups still fit the kMtileSlots CUs in one round.
+    // Llama-70B TP=1 at M = 64 (MLP): 109.5 us with 64 x 256 tiles of 4 waves
+    // in 512 slots (two per CU), 106.3 us here (GEMM2 52.4 -> 48.9 us: 8 waves
+    // share one copy of the activations); more splits than fit one round are
+    // slower (8 waves in 320 slots: GEMM1 280 workgroups, 144 us), and so is
+    // one wave per SIMD
     q.rt = 4;
-    q.nw = 8;
-    q.st = 2;
-    const int nblk = (K + 127) / 128;
     const int tiles = ((M + 63) / 64) * ((N + 511) / 512);
-    int ks = kMtileSlots / tiles;
-    ks = std::max(1, std::min(ks, nblk / 4));
-    if ((int64_t)ks * M * N * 4 >= lim) ks = 1;
-    q.ks = ks;
+    q.ks = std::max(1, std::min(kMtileSlots / tiles, nblk / 4));
+    if ((int64_t)q.ks * M * N * 4 >= lim) q.ks = 1;
+    *p = q;
+    return true;
   }
-  *p = q;
+  // the gated product and smaller weights below prefill sizes keep their
+  // weights exact, as the decode kernels that otherwise run them do
+  const bool exact = gated || M < kPrefillMinM;
+  if (exact && (!optional || M <= kDecodeMaxM)) return false;
+  // 128 x 512 tiles over the whole K, or 64 x 512 ones, or either with K
+  // split, whichever fills the CUs better (mtile_cost); Llama-70B TP=8 GEMM2
+  // at M = 1000: 128 tiles of 128 x 512 on 256 CUs 84.7 us, 256 of 64 x 512
+  // 67.8 us; 6144 x 6144 at M = 512: 133.6 us, 57.5 us with 64-row tiles and
+  // K split 2
+  double best = 1e30;
+  for (int rt : {8, 4}) {
+    if (exact && rt == 8) continue;
+    for (int ks = 1; ks <= std::max(1, nblk / 4); ++ks) {
+      MtilePlan c = q;
+      c.rt = rt;
+      c.ks = ks;
+      c.exact = exact;
+      if (ks > 1 && (!optional || mtile_part_bytes(c, M, N) > part_budget ||
+                     (int64_t)ks * M * N * (gated ? 8 : 4) >= lim))
+        break;
+      const double cost = mtile_cost(M, N, nblk, rt, ks, gated, exact, dt);
+      if (cost < 0.98 * best) {
+        best = cost;
+        *p = c;
+      }
+    }
+  }
   return true;
 }
 
 size_t mtile_part_bytes(const MtilePlan& p, int M, int N) {
-  return p.ks > 1 ? align_up((size_t)p.ks * M * N * 4) : 0;
+  return p.ks > 1 ? align_up((size_t)p.ks * M * N * (p.gated ? 8 : 4)) : 0;
 }
 
-template <int NW, int ST, int RT, int DT>
+template <int RT, int DT, bool EXACT, bool GATED>
 hipError_t launch_mtile_t(const GemmArgs& a, int ks, hipStream_t s) {
+  constexpr int NW = 8, ST = 2;
   typedef void (*Kern)(GemmArgs);
   Kern k = nullptr;
   switch (a.G / 32) {
-    case 1: k = k_prefill<1, NW, ST, RT, DT>; break;
-    case 2: k = k_prefill<2, NW, ST, RT, DT>; break;
-    case 4: k = k_prefill<4, NW, ST, RT, DT>; break;
-    case 8: k = k_prefill<8, NW, ST, RT, DT>; break;
+    case 1: k = k_prefill<1, NW, ST, RT, DT, EXACT, GATED>; break;
+    case 2: k = k_prefill<2, NW, ST, RT, DT, EXACT, GATED>; break;
+    case 4: k = k_prefill<4, NW, ST, RT, DT, EXACT, GATED>; break;
+    case 8: k = k_prefill<8, NW, ST, RT, DT, EXACT, GATED>; break;
   }
   if (!k) return hipErrorInvalidValue;
-  const int lds = ST * pf_stage(RT, NW);
+  const int lds = ST * pf_stage(RT, NW, GATED);
   hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return e;
-  const int grid = ((a.M + 16 * RT - 1) / (16 * RT)) * ((a.N + 64 * NW - 1) / (64 * NW)) * ks;
+  const int bn = (GATED ? 32 : 64) * NW;
+  const int grid = ((a.M + 16 * RT - 1) / (16 * RT)) * ((a.N + bn - 1) / bn) * ks;
   hipLaunchKernelGGL(k, dim3(grid), dim3(NW * 64), lds, s, a);
   return hipGetLastError();
+}
+
+template <int DT>
+hipError_t launch_mtile_dt(const GemmArgs& a, const MtilePlan& p, hipStream_t s) {
+  if (p.nw != 8 || p.st != 2) return hipErrorInvalidValue;
+  if (p.gated) return p.rt == 4 && p.exact ? launch_mtile_t<4, DT, true, true>(a, p.ks, s) : hipErrorInvalidValue;
+  if (p.rt == 4)
+    return p.exact ? launch_mtile_t<4, DT, true, false>(a, p.ks, s)
+                   : launch_mtile_t<4, DT, false, false>(a, p.ks, s);
+  return p.rt == 8 && !p.exact ? launch_mtile_t<8, DT, false, false>(a, p.ks, s) : hipErrorInvalidValue;
 }
 
 hipError_t launch_mtile(const GemmArgs& a0, const MtilePlan& p, float* part, hipStream_t s) {
@@ -439,27 +584,21 @@ hipError_t launch_mtile(const GemmArgs& a0, const MtilePlan& p, float* part, hip
   a.ks = p.ks;
   a.part = part;
   if (p.ks > 1 && !part) return hipErrorInvalidValue;
-  hipError_t e;
-  const bool bf = a.dt == kBF16;
-  if (p.rt == 8 && p.nw == 8 && p.st == 2)
-    e = bf ? launch_mtile_t<8, 2, 8, kBF16>(a, p.ks, s) : launch_mtile_t<8, 2, 8, kF16>(a, p.ks, s);
-  else if (p.rt == 4 && p.nw == 8 && p.st == 2)
-    e = bf ? launch_mtile_t<8, 2, 4, kBF16>(a, p.ks, s) : launch_mtile_t<8, 2, 4, kF16>(a, p.ks, s);
-  else
-    return hipErrorInvalidValue;
+  const hipError_t e = a.dt == kBF16 ? launch_mtile_dt<kBF16>(a, p, s) : launch_mtile_dt<kF16>(a, p, s);
   if (e != hipSuccess || p.ks == 1) return e;
-  return launch_splitk_reduce(part, p.ks, a.M, a.N, a.Y, a.ldy, a.dt, s);
+  return launch_splitk_reduce(part, p.ks, a.M, a.N, a.Y, a.ldy, a.dt, p.gated, s);
 }
 
 hipError_t launch_splitk_reduce(const float* part, int ks, int M, int N, uint16_t* Y, int64_t ldy,
-                                int dt, hipStream_t s) {
+                                int dt, bool gated, hipStream_t s) {
   const int64_t total = (int64_t)M * N / 4 + 1;
   const int blocks = (int)std::min<int64_t>((total + 255) / 256, 16384);
-  if (dt == kBF16)
-    hipLaunchKernelGGL(k_splitk_reduce<kBF16>, dim3(blocks), dim3(256), 0, s, part, ks, M, N, Y, ldy);
-  else
-    hipLaunchKernelGGL(k_splitk_reduce<kF16>, dim3(blocks), dim3(256), 0, s, part, ks, M, N, Y, ldy);
-  return hipGetLastError();
+  auto go = [&](auto k) {
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, s, part, ks, M, N, Y, ldy);
+    return hipGetLastError();
+  };
+  if (dt == kBF16) return gated ? go(k_splitk_reduce<kBF16, true>) : go(k_splitk_reduce<kBF16, false>);
+  return gated ? go(k_splitk_reduce<kF16, true>) : go(k_splitk_reduce<kF16, false>);
 }
 
 hipError_t launch_gather_rows(const uint16_t* X, int64_t ldx, int M, int K, const int32_t* perm,

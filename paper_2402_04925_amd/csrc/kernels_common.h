@@ -212,6 +212,9 @@ __device__ __forceinline__ f4_t mfma_k32(u4_t a, u4_t b, f4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(a), as_h8(b), c, 0, 0, 0);
 }
 
+// silu(g) * u in fp32
+__device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.f + __expf(-g)) * u; }
+
 // Workgroups are dispatched round-robin over the 8 XCDs. Neighbouring
 // 16-column tiles share 128-byte lines of scales (and, in the GPTQ layout, of
 // qweight), so consecutive tiles go to workgroups on the same XCD (same L2).

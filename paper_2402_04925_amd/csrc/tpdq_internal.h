@@ -152,14 +152,20 @@ constexpr int64_t kMtileMinWeights = (int64_t)64 << 20;
 constexpr int kMtileSlots = 256;  // one 8-wave workgroup per CU on 256 CUs
 struct MtilePlan {
   int rt, nw, st, ks;  // row tiles and waves per workgroup, LDS stages, K splits
+  bool exact;          // q - z in the MFMAs, scales in fp32 (else weights rounded)
+  bool gated;          // Y = silu(X W) * (X W_up)
 };
-bool plan_mtile(int M, int64_t ldx, const tpdq_w4* w, int meta, MtilePlan* p);
+// optional: also the plans that only serve as a faster route than another one
+// (exact, or a K split at prefill sizes), with partials of at most part_budget
+// bytes
+bool plan_mtile(int M, int64_t ldx, const tpdq_w4* w, int meta, int dt, bool gated, bool optional,
+                size_t part_budget, MtilePlan* p);
 // workspace bytes of the fp32 partials (0 when ks == 1)
 size_t mtile_part_bytes(const MtilePlan& p, int M, int N);
 // part: the partials (ignored when p.ks == 1)
 hipError_t launch_mtile(const GemmArgs& a, const MtilePlan& p, float* part, hipStream_t s);
 hipError_t launch_splitk_reduce(const float* part, int ks, int M, int N, uint16_t* Y, int64_t ldy,
-                                int dt, hipStream_t s);
+                                int dt, bool gated, hipStream_t s);
 // Xp [M][K] = X[:, perm] row-major (for the prefill GEMM's activations)
 hipError_t launch_gather_rows(const uint16_t* X, int64_t ldx, int M, int K, const int32_t* perm,
                               uint16_t* Xp, hipStream_t s);
