@@ -16,7 +16,7 @@ CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libtpdq.so")
 SOURCES = ["abi.hip", "gemm_decode.hip", "gemm_decode_bf16.hip", "gemm_gated.hip", "gemm_gated_bf16.hip",
-           "gemm_prefill.hip", "reorder.hip"]
+           "gemm_prefill.hip", "gemm_actorder.hip", "reorder.hip"]
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [

@@ -124,6 +124,21 @@ bool mtile_for(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, int dt
                     optional ? avail - gather : 0, p);
 }
 
+// The dequantize-once plan of a call whose rows take their metadata one by one
+// (act-order, or sorted rows whose groups are not whole 32-row steps; the
+// path that reads metadata from global memory row by row stays as drawn in
+// Fig. 1), where `avail` bytes of workspace hold it. *gather: the bytes of
+// X[:, perm] before it.
+bool dense_for(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, bool gated, size_t avail,
+               size_t* gather, DensePlan* p) {
+  const int G = w->group_size;
+  const bool rows = meta == kMetaRowLds ||
+                    (meta == kMetaGroup && G != 32 && G != 64 && G != 128 && G != 256);
+  if (!rows || (perm && (size_t)w->K * 2 > kLdsMax)) return false;
+  *gather = mtile_gather_bytes(M, w->K, perm);
+  return avail > *gather && plan_dense16(M, perm ? (int64_t)w->K : ldx, w, gated, avail - *gather, p);
+}
+
 // The decode plan of one launch of mc <= 64 rows, as run_gemm makes it: with
 // a perm, the gather inside the kernel's LDS if it is planned; else, up to 4
 // rows, X' gathered once row-major when the tile kernel then takes it like
@@ -166,6 +181,10 @@ size_t gemm_ws_need(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, i
   MtilePlan p;
   if (mtile_for(M, ldx, perm, w, meta, dt, gated, avail, &p))
     return mtile_gather_bytes(M, w->K, perm) + mtile_part_bytes(p, M, w->N);
+  DensePlan ep;
+  size_t gather = 0;
+  if (dense_for(M, ldx, perm, w, meta, gated, avail, &gather, &ep))
+    return gather + ep.w_bytes + ep.part_bytes;
   DecodePlan dp;
   bool prepared = false;
   const int mc = std::min(M, kDecodeMaxM);  // the largest launch
@@ -205,8 +224,12 @@ tpdq_status run_gemm(const uint16_t* X, int64_t ldx, int M, const int32_t* perm,
   const int32_t* gidx = path == TPDQ_PATH_ORDERED && w->group_size > 0 ? nullptr : w->g_idx;
   MtilePlan mp;
   const bool gated = io.up != nullptr;
-  if (mtile_for(M, ldx, perm != nullptr, w, meta, dt, gated, ws ? ws_bytes : kBaseWs, &mp)) {
-    // M-tiled MFMA GEMM over all rows, the activations gathered first
+  const size_t avail = ws ? ws_bytes : kBaseWs;
+  DensePlan ep;
+  size_t gather = 0;
+  const bool mtile = mtile_for(M, ldx, perm != nullptr, w, meta, dt, gated, avail, &mp);
+  if (mtile || dense_for(M, ldx, perm != nullptr, w, meta, gated, avail, &gather, &ep)) {
+    // an MFMA GEMM over all rows, the activations gathered first
     const uint16_t* Xa = X;
     int64_t lda = ldx;
     if (perm) {
@@ -226,6 +249,7 @@ tpdq_status run_gemm(const uint16_t* X, int64_t ldx, int M, const int32_t* perm,
     a.lds = w->ld_s;
     a.qz = (const uint32_t*)w->qzeros;
     a.ldz = w->ld_z;
+    a.g_idx = gidx;
     a.K = w->K;
     a.N = w->N;
     a.G = w->group_size;
@@ -239,9 +263,14 @@ tpdq_status run_gemm(const uint16_t* X, int64_t ldx, int M, const int32_t* perm,
     }
     a.Y = Y;
     a.ldy = ldy;
-    float* part = (float*)(ws + mtile_gather_bytes(M, w->K, perm != nullptr));
-    hipError_t e = launch_mtile(a, mp, part, st);
-    if (e != hipSuccess) return hip_fail(e, "M-tiled GEMM launch");
+    hipError_t e;
+    if (mtile) {
+      e = launch_mtile(a, mp, (float*)(ws + mtile_gather_bytes(M, w->K, perm != nullptr)), st);
+      if (e != hipSuccess) return hip_fail(e, "M-tiled GEMM launch");
+    } else {
+      e = launch_dense16(a, ep, w->layout, ws + gather, st);
+      if (e != hipSuccess) return hip_fail(e, "dequantized GEMM launch");
+    }
     return TPDQ_OK;
   }
   for (int m0 = 0; m0 < M; m0 += kDecodeMaxM) {
@@ -391,9 +420,11 @@ size_t ws_bound(int op, int32_t M, const tpdq_w4* a, const tpdq_w4* b, size_t av
   auto gemm_max = [&](const tpdq_w4* w, bool perm_possible, bool gated) {
     size_t n = perm_possible ? decode_gather_bytes(M, w->K) : 0;
     for (int pm = 0; pm <= (perm_possible ? 1 : 0); ++pm)
-      for (int meta : {kMetaGroup, kMetaRowLds, kMetaRowGlobal})
+      for (int meta : {kMetaGroup, kMetaRowLds, kMetaRowGlobal}) {
+        if (meta == kMetaRowLds && !w->g_idx) continue;  // no act-order path without one
         for (int dt : {TPDQ_FP16, TPDQ_BF16})
           n = std::max(n, gemm_ws_need(M, w->K, pm == 1, w, meta, dt, gated, avail));
+      }
     return n;
   };
   if (op == 1) return gemm_max(a, true, false);

@@ -49,17 +49,6 @@ __host__ __device__ constexpr int pf_stage(int rt, int nw, bool gated) {
   return rt * 4 * 64 * 16 + nw * (kPWwave + pf_meta(gated));
 }
 
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-
-template <int BYTES>
-__device__ __forceinline__ void dma_to_lds(__amdgpu_buffer_rsrc_t r, void* dst, uint32_t off) {
-  static_assert(BYTES == 4 || BYTES == 16, "4- or 16-byte records");
-  if constexpr (BYTES == 16)
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)dst, 16, off, 0, 0, 0);
-  else
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)dst, 4, off, 0, 0, 0);
-}
-
 __device__ __forceinline__ u4_t dequant_scaled(const UnpackConsts<kF16>& kc, uint32_t w, uint32_t z1024,
                                                uint32_t z64, uint32_t s2) {
   const h8_t d = unpack_sub(kc, w, z1024, z64);

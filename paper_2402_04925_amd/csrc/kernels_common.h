@@ -249,5 +249,17 @@ __device__ __forceinline__ uint32_t buffer_load2(__amdgpu_buffer_rsrc_t r, uint3
   return __builtin_amdgcn_raw_buffer_load_b16(r, off, 0, 0);
 }
 
+typedef __attribute__((address_space(3))) void* lds_ptr_t;
+
+// one record of 64 lanes from global memory straight to LDS (dst + lane * BYTES)
+template <int BYTES>
+__device__ __forceinline__ void dma_to_lds(__amdgpu_buffer_rsrc_t r, void* dst, uint32_t off) {
+  static_assert(BYTES == 4 || BYTES == 16, "4- or 16-byte records");
+  if constexpr (BYTES == 16)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)dst, 16, off, 0, 0, 0);
+  else
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)dst, 4, off, 0, 0, 0);
+}
+
 }  // namespace
 }  // namespace tpdq

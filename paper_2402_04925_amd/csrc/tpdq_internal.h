@@ -166,6 +166,20 @@ size_t mtile_part_bytes(const MtilePlan& p, int M, int N);
 hipError_t launch_mtile(const GemmArgs& a, const MtilePlan& p, float* part, hipStream_t s);
 hipError_t launch_splitk_reduce(const float* part, int ks, int M, int N, uint16_t* Y, int64_t ldy,
                                 int dt, bool gated, hipStream_t s);
+// Per-row metadata at more than 64 rows (gemm_actorder.hip): the weights are
+// dequantized to 16 bits in operand order, a chunk of columns at a time, and
+// multiplied by a dense MFMA kernel. A chunk takes at most kDenseChunkBytes
+// (half the 256 MB last-level cache, where it stays between its two kernels).
+constexpr size_t kDenseChunkBytes = (size_t)128 << 20;
+struct DensePlan {
+  int rt, ks;          // row tiles per workgroup, K splits
+  int ncols;           // columns per chunk
+  size_t w_bytes;      // of the chunk's 16-bit weights (gate and up when gated)
+  size_t part_bytes;   // of its split-K partials
+};
+bool plan_dense16(int M, int64_t ldx, const tpdq_w4* w, bool gated, size_t budget, DensePlan* p);
+// a.qw_up: the gated product; ws: p.w_bytes + p.part_bytes
+hipError_t launch_dense16(const GemmArgs& a, const DensePlan& p, int layout, char* ws, hipStream_t s);
 // Xp [M][K] = X[:, perm] row-major (for the prefill GEMM's activations)
 hipError_t launch_gather_rows(const uint16_t* X, int64_t ldx, int M, int K, const int32_t* perm,
                               uint16_t* Xp, hipStream_t s);
