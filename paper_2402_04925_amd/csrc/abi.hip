@@ -145,10 +145,22 @@ bool dense_for(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, bool g
 // any X (*plain); else the prepared operand (*prepared). The workspace of the
 // prepared operand is at least that of the row-major X', so sizes computed
 // without `plain` cover both.
+// Per-row metadata without a perm: the operand is prepared too (a copy in
+// operand order) where `avail` bytes of workspace hold it, from 17 rows on, or
+// 12 on weights of 16M elements: row-major loads touch 16 rows a row apart.
+// 6144 x 6144 act-order GEMM with the copy: M = 64 59.7 -> 38.1 us, M = 32
+// 33.0 -> 24.4, M = 16 23.7 -> 20.8; 2048 x 2048 at M = 16 8.9 -> 8.6, M = 8
+// 7.3 -> 8.5 (the copy is a launch of its own).
 bool decode_plan_for(int mc, bool perm, const tpdq_w4* w, int meta, int dt, DecodePlan* plan,
-                     bool* prepared, bool gated = false, bool* plain = nullptr) {
+                     bool* prepared, bool gated, bool* plain, size_t avail) {
   *prepared = false;
   if (plain) *plain = false;
+  if (!perm && meta != kMetaGroup && (mc > 16 || (mc >= 12 && (int64_t)w->K * w->N >= kWideMinWeightsRowMajor)) &&
+      avail != kBaseWs && avail >= decode_gather_bytes(mc, w->K)) {
+    *prepared = true;
+    return plan_decode(mc, w->K, w->N, w->group_size, w->num_groups, w->layout, meta, kOperandPrepared, dt,
+                       plan, gated);
+  }
   if (perm) {
     if (plan_decode(mc, w->K, w->N, w->group_size, w->num_groups, w->layout, meta, kOperandGather,
                     dt, plan, gated))
@@ -188,7 +200,7 @@ size_t gemm_ws_need(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, i
   DecodePlan dp;
   bool prepared = false;
   const int mc = std::min(M, kDecodeMaxM);  // the largest launch
-  if (!decode_plan_for(mc, perm, w, meta, dt, &dp, &prepared, gated))
+  if (!decode_plan_for(mc, perm, w, meta, dt, &dp, &prepared, gated, nullptr, avail))
     return perm ? decode_gather_bytes(M, w->K) : 0;
   const size_t part = decode_part_bytes(dp, mc, w->N);
   return (prepared || part ? decode_gather_bytes(M, w->K) : 0) + part;
@@ -283,9 +295,9 @@ tpdq_status run_gemm(const uint16_t* X, int64_t ldx, int M, const int32_t* perm,
                         ? plan_decode(mc, w->K, w->N, w->group_size, w->num_groups, w->layout, meta,
                                       kOperandPrepared, dt, &plan, gated)
                         : decode_plan_for(mc, perm != nullptr, w, meta, dt, &plan, &prepared, gated,
-                                          &plain);
+                                          &plain, avail);
     const int operand =
-        perm ? (prepared ? kOperandPrepared : (plain ? kOperandPlain : kOperandGather)) : kOperandPlain;
+        prepared ? kOperandPrepared : (perm && !plain ? kOperandGather : kOperandPlain);
     if (ok && plain) {
       uint16_t* Xp = (uint16_t*)ws;
       hipError_t e = launch_gather_plain(Xc, ldx, mc, w->K, perm, Xp, st);
@@ -354,17 +366,29 @@ bool mlp_prepared_y1(int M, int64_t ldx, bool perm, const tpdq_w4* w1, const tpd
     return false;
   DecodePlan p1, p2;
   bool prepared = false;
-  if (!decode_plan_for(M, perm, w1, meta, dt, &p1, &prepared, gated) || p1.wide) return false;
+  if (!decode_plan_for(M, perm, w1, meta, dt, &p1, &prepared, gated, nullptr, kBaseWs) || p1.wide) return false;
   // GEMM2 would read row-major Y1 from global memory: through the tile
   // kernel, or through k_wide only because of the row-major rule (on
   // weights of kWideMinWeights or more GEMM2 stays on k_wide instead)
   const bool big2 = (int64_t)w2->K * w2->N >= kWideMinWeights;
-  if (!decode_plan_for(M, false, w2, meta, dt, &p2, &prepared) || (p2.wide && big2) ||
+  if (!decode_plan_for(M, false, w2, meta, dt, &p2, &prepared, false, nullptr, kBaseWs) || (p2.wide && big2) ||
       p2.amode != kAGlobal)
     return false;
   DecodePlan p3;
   return plan_decode(M, w2->K, w2->N, w2->group_size, w2->num_groups, w2->layout, meta,
                      kOperandPrepared, dt, &p3) && !p3.wide;
+}
+
+// Offset of Y1's operand-order copy in a workspace of ws_bytes, behind what
+// GEMM1 uses; *ws1: the bytes GEMM1's route is chosen for (its base route where
+// a faster one would leave no room for the copy).
+size_t y1_offset(int M, int64_t ldx, bool perm, const tpdq_w4* w1, int meta, int dt, bool gated,
+                 size_t ws_bytes, size_t* ws1) {
+  const size_t off = gemm_ws_need(M, ldx, perm, w1, meta, dt, gated, ws_bytes);
+  *ws1 = ws_bytes;
+  if (off + decode_gather_bytes(M, w1->N) <= ws_bytes) return off;
+  *ws1 = kBaseWs;
+  return gemm_ws_need(M, ldx, perm, w1, meta, dt, gated, kBaseWs);
 }
 
 // The device address of each GPU's copy of `scratch`, taken once per device.
@@ -644,14 +668,14 @@ tpdq_status mlp_shard(const void* X, int64_t ldx, int32_t M, const int32_t* P1, 
   hipStream_t s = (hipStream_t)stream;
   char* ws = (char*)workspace;
   GemmIO io1, io2;
+  size_t ws1 = ws_bytes;
   if (workspace && ws_bytes >= bound && mlp_prepared_y1(M, ldx, !act, w1, w2, meta, dtype)) {
-    const size_t off = gemm_ws_need(M, ldx, !act, w1, meta, dtype, false, kBaseWs);
-    io1.yp = (uint16_t*)(ws + off);
+    io1.yp = (uint16_t*)(ws + y1_offset(M, ldx, !act, w1, meta, dtype, false, ws_bytes, &ws1));
     io1.yp_natural = w2->layout == TPDQ_LAYOUT_TILED ? 1 : 0;
     io2.x_prepared = true;
   }
   st = run_gemm((const uint16_t*)X, ldx, M, act ? nullptr : P1, w1, path, dtype, (uint16_t*)Y1, w1->N,
-                ws, ws_bytes, s, io1);
+                ws, ws1, s, io1);
   if (st != TPDQ_OK) return st;
   if (io2.x_prepared)
     return run_gemm(io1.yp, w1->N, M, nullptr, w2, path, dtype, (uint16_t*)Y2_partial, w2->N, ws, ws_bytes,
@@ -720,13 +744,14 @@ tpdq_status tpdq_gated_mlp_shard(const void* X, int64_t ldx, int32_t M, const in
   char* ws = (char*)workspace;
   GemmIO io1, io2;
   io1.up = w_up;
+  size_t ws1 = ws_bytes;
   if (workspace && ws_bytes >= bound && mlp_prepared_y1(M, ldx, !act, w_gate, w_down, meta, dtype, true)) {
-    io1.yp = (uint16_t*)(ws + gemm_ws_need(M, ldx, !act, w_gate, meta, dtype, true, kBaseWs));
+    io1.yp = (uint16_t*)(ws + y1_offset(M, ldx, !act, w_gate, meta, dtype, true, ws_bytes, &ws1));
     io1.yp_natural = w_down->layout == TPDQ_LAYOUT_TILED ? 1 : 0;
     io2.x_prepared = true;
   }
   st = run_gemm((const uint16_t*)X, ldx, M, act ? nullptr : P1, w_gate, path, dtype, (uint16_t*)Y1,
-                w_gate->N, ws, ws_bytes, s, io1);
+                w_gate->N, ws, ws1, s, io1);
   if (st != TPDQ_OK) return st;
   if (io2.x_prepared)
     return run_gemm(io1.yp, w_gate->N, M, nullptr, w_down, path, dtype, (uint16_t*)Y2_partial,

@@ -65,10 +65,12 @@ __device__ __forceinline__ void load_groups(const GemmArgs& a, bool ok, int wr, 
 // registers is copied afterwards, four loads in flight at a time.
 // ---------------------------------------------------------------------------
 
-// Metadata of the 16-column tile (kMetaRowLds), one 16-byte entry per
-// (group, column): the scale's bits | z << 16 in word COMP (0; the gated
-// kernel's up projection in word 1).
-template <int NT, int R, int COMP = 0>
+// Metadata of the 16-column tile (kMetaRowLds): one entry of W words per
+// (group, column), the scale's bits | (0x6400 | z) << 16 (the zero as fp16
+// 1024 + z) in word COMP (0; the gated kernel's up projection in word 1 of 2).
+// Entries of 4 (8) bytes: a wave's 64 lanes read four groups' 16 neighbouring
+// words, at 16 bytes apart they met on a quarter of the banks.
+template <int NT, int R, int W, int COMP = 0>
 struct MetaStage {
   uint32_t s[R], z[R];
   // Entry idx = 16 g + c: group g, column n0 + c. The loads are branch-free:
@@ -87,15 +89,15 @@ struct MetaStage {
     for (int i = 0; i < R; ++i) fetch(a, n0, rows, tid + i * NT, s[i], z[i]);
   }
   // the stored zero code plus the layer's offset (up to 16) in the high half
-  __device__ __forceinline__ static void put(u4_t* meta, int idx, int n, uint32_t sbits,
+  __device__ __forceinline__ static void put(uint32_t* meta, int idx, int n, uint32_t sbits,
                                              uint32_t zw, int zoff) {
     const uint32_t zc = ((zw >> (4 * (n & 7))) & 0xFu) + (uint32_t)zoff;
-    ((uint32_t*)&meta[idx])[COMP] = sbits | (zc << 16);
+    meta[idx * W + COMP] = sbits | ((0x6400u | zc) << 16);
   }
   // Entries past the last group go to the spare entry meta[items], so every
   // value loaded in load() is consumed on every path (a value used only
   // under a branch lets the compiler sink its load behind the weight loads).
-  __device__ __forceinline__ void store(const GemmArgs& a, u4_t* meta, int n0, int rows, int tid) {
+  __device__ __forceinline__ void store(const GemmArgs& a, uint32_t* meta, int n0, int rows, int tid) {
     const int items = rows * kTileN;
 #pragma unroll
     for (int i = 0; i < R; ++i) {
@@ -115,6 +117,32 @@ struct MetaStage {
     }
   }
 };
+
+// Groups of the K rows (kMetaRowLds) in LDS: per row the byte offset of its
+// group's 16 entries (>> SH), clamped into the tile's metadata, in 16 bits.
+// Staged once per workgroup: read from global memory they would cost every
+// lane of the 16 columns its own 32 bytes, a clamp and a multiply per word.
+template <int NT, int SH>
+__device__ __forceinline__ void stage_groups(const GemmArgs& a, uint16_t* gl, int rows, int tid) {
+  const uint32_t gmax = (uint32_t)(rows - 1);
+  const int kp = 128 * ((a.K + 127) >> 7);
+  for (int k = 4 * tid; k < kp; k += 4 * NT) {
+    uint32_t g[4] = {0u, 0u, 0u, 0u};
+    if (k < a.K) {
+      if (a.g_idx) {
+        const u4_t v = *(const u4_t*)(a.g_idx + k);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) g[e] = v[e];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) g[e] = (uint32_t)(k + e) / (uint32_t)a.G;
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) g[e] = min(g[e], gmax) << 6;  // 16 entries of 4 bytes << SH
+    }
+    *(uint2*)(gl + k) = make_uint2(g[0] | (g[1] << 16), g[2] | (g[3] << 16));
+  }
+}
 
 // Activations in operand order: LDS entry (r * M + m) holds row m, rows
 // 8r..8r+7 of the operand (permuted as x0, x4, x1, x5, x2, x6, x3, x7 for
@@ -1005,7 +1033,11 @@ __global__ __launch_bounds__(NW * 64) void k_wide(GemmArgs a) {
 // ---------------------------------------------------------------------------
 // Row-metadata kernel: each of the 8 rows of a word looks its group up
 // (g_idx, or floor(k / G) when g_idx is NULL) and is dequantized on its own.
-// One 128-row block of weights (and of g_idx) is prefetched ahead.
+// One 128-row block of weights (and, kMetaRowGlobal, of g_idx) is prefetched
+// ahead. kMetaRowLds is bound by its VALU and LDS work per word, 8 lookups and
+// 8 dequantizations: the tile's metadata and every row's entry offset are in
+// LDS, so that a lookup is one address operation and one 4-byte read, and two
+// byte permutes make the zero and scale pairs of packed fp16 arithmetic.
 // ---------------------------------------------------------------------------
 template <int MT, int NW, int META, int AM, int LAYOUT, int DT, bool GATED = false>
 __global__ __launch_bounds__(NW * 64) void k_rowmeta(GemmArgs a) {
@@ -1027,7 +1059,9 @@ __global__ __launch_bounds__(NW * 64) void k_rowmeta(GemmArgs a) {
   const int nblk = (a.K + 127) >> 7;
   const int b0 = (int)((int64_t)nblk * wave / NW);
   const int b1 = (int)((int64_t)nblk * (wave + 1) / NW);
-  u4_t* meta = (u4_t*)smem;
+  constexpr int MW = GATED ? 2 : 1;  // words per metadata entry
+  uint32_t* meta = (uint32_t*)smem;
+  uint16_t* gl = (uint16_t*)(smem + a.lds_g_off);
   u4_t* xs = (u4_t*)(smem + a.lds_x_off);
   const int zero_slot = a.M * 16 * nblk;
   const uint32_t* qcol = a.qw + col;
@@ -1043,14 +1077,16 @@ __global__ __launch_bounds__(NW * 64) void k_rowmeta(GemmArgs a) {
   const uint32_t* qcol_u = au.qw + col;
   const uint32_t* qtile_u = au.qw + (int64_t)tile * a.ldq;
 
-  MetaStage<NT, 8> ms;
-  MetaStage<NT, 8, 1> msu;
+  constexpr int MR = 4096 / NT < 8 ? 4096 / NT : 8;
+  MetaStage<NT, MR, MW> ms;
+  MetaStage<NT, MR, MW, MW - 1> msu;
   if constexpr (META == kMetaRowLds) ms.load(a, n0, a.meta_rows, tid);
   if constexpr (META == kMetaRowLds && GATED) msu.load(au, n0, a.meta_rows, tid);
   XStage<NT, false, LAYOUT> xst;
   if constexpr (!AG) xst.load(a, tid);
 
   auto load_g = [&](int b, u4_t (&g)[4][2]) {
+    if constexpr (META == kMetaRowLds) return;  // in LDS
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int wr = 4 * (4 * b + u) + kq;
@@ -1067,6 +1103,7 @@ __global__ __launch_bounds__(NW * 64) void k_rowmeta(GemmArgs a) {
 
   if constexpr (META == kMetaRowLds) ms.store(a, meta, n0, a.meta_rows, tid);
   if constexpr (META == kMetaRowLds && GATED) msu.store(au, meta, n0, a.meta_rows, tid);
+  if constexpr (META == kMetaRowLds) stage_groups<NT, MW - 1>(a, gl, a.meta_rows, tid);
   if constexpr (!AG) xst.store(a, xs, nullptr, tid);
   if constexpr (META == kMetaRowLds || !AG) __syncthreads();
   AAddr aa[MT];
@@ -1104,23 +1141,30 @@ __global__ __launch_bounds__(NW * 64) void k_rowmeta(GemmArgs a) {
         else
           av[t] = xs[aa[t].base + aa[t].stride * (4 * b + u)];
       }
-      uint32_t zr[8], sr[8], zru[8], sru[8];
+      u4_t bv, bvu;
+      if constexpr (META == kMetaRowLds) {
+        // the eight rows' entry offsets, two to a word
+        const u4_t gp = *(const u4_t*)(gl + 128 * b + 32 * u + 8 * kq);
+        uint32_t e[8], eu[8];
 #pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const uint32_t g = min(r < 4 ? gb[u][0][r] : gb[u][1][r - 4], gmax);
-        if constexpr (META == kMetaRowLds) {
+        for (int r = 0; r < 8; ++r) {
+          const uint32_t o16 = (r & 1) ? gp[r >> 1] >> 16 : gp[r >> 1] & 0xFFFFu;
+          const unsigned char* p = smem + ((o16 << (MW - 1)) | (uint32_t)(4 * MW * j));
           if constexpr (GATED) {
-            const uint2 v = *(const uint2*)&meta[g * kTileN + j];
-            zr[r] = v.x >> 16;
-            sr[r] = v.x & 0xFFFFu;
-            zru[r] = v.y >> 16;
-            sru[r] = v.y & 0xFFFFu;
+            const uint2 v = *(const uint2*)p;
+            e[r] = v.x;
+            eu[r] = v.y;
           } else {
-            const uint32_t v = meta[g * kTileN + j].x;
-            zr[r] = v >> 16;
-            sr[r] = v & 0xFFFFu;
+            e[r] = *(const uint32_t*)p;
           }
-        } else {
+        }
+        bv = dequant_entries<LAYOUT == TPDQ_LAYOUT_TILED, DT>(kc, wb[u], e);
+        if constexpr (GATED) bvu = dequant_entries<LAYOUT == TPDQ_LAYOUT_TILED, DT>(kc, wbu[u], eu);
+      } else {
+        uint32_t zr[8], sr[8], zru[8], sru[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          const uint32_t g = min(r < 4 ? gb[u][0][r] : gb[u][1][r - 4], gmax);
           sr[r] = col_ok ? (uint32_t)a.sc[(int64_t)g * a.lds + col] : 0u;
           zr[r] = col_ok ? ((a.qz[(int64_t)g * a.ldz + (col >> 3)] >> zshift) & 0xFu) + zoff : 0u;
           if constexpr (GATED) {
@@ -1128,12 +1172,12 @@ __global__ __launch_bounds__(NW * 64) void k_rowmeta(GemmArgs a) {
             zru[r] = col_ok ? ((au.qz[(int64_t)g * a.ldz + (col >> 3)] >> zshift) & 0xFu) + zoff : 0u;
           }
         }
+        bv = dequant_rows<LAYOUT == TPDQ_LAYOUT_TILED, DT>(kc, wb[u], zr, sr);
+        if constexpr (GATED) bvu = dequant_rows<LAYOUT == TPDQ_LAYOUT_TILED, DT>(kc, wbu[u], zru, sru);
       }
-      const u4_t bv = dequant_rows<LAYOUT == TPDQ_LAYOUT_TILED, DT>(kc, wb[u], zr, sr);
 #pragma unroll
       for (int t = 0; t < MT; ++t) acc[t] = mfma_k32<DT>(av[t], bv, acc[t]);
       if constexpr (GATED) {
-        const u4_t bvu = dequant_rows<LAYOUT == TPDQ_LAYOUT_TILED, DT>(kc, wbu[u], zru, sru);
 #pragma unroll
         for (int t = 0; t < MT; ++t) accu[t] = mfma_k32<DT>(av[t], bvu, accu[t]);
       }
@@ -1141,10 +1185,12 @@ __global__ __launch_bounds__(NW * 64) void k_rowmeta(GemmArgs a) {
     if (more) {
       wb = wn;
       if constexpr (GATED) wbu = wnu;
+      if constexpr (META != kMetaRowLds) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        gb[u][0] = gn[u][0];
-        gb[u][1] = gn[u][1];
+        for (int u = 0; u < 4; ++u) {
+          gb[u][0] = gn[u][0];
+          gb[u][1] = gn[u][1];
+        }
       }
       if constexpr (AG) {
 #pragma unroll
@@ -1221,9 +1267,9 @@ DecodeKernel pick_row_am(int am) {
 template <int MT, int NW, int L, int DT>
 DecodeKernel pick_mt_nw(const DecodePlan& p) {
   if (p.meta == kMetaGroup) return pick_ordered_spg<MT, NW, L, DT>(p.spg, p.amode, p.tn);
-  if constexpr (NW <= 8 && !(MT == 4 && NW > 4)) {
+  if constexpr (!(MT == 4 && NW > 4) && (NW <= 8 || MT == 1)) {
     if (p.meta == kMetaRowLds) return pick_row_am<MT, NW, L, kMetaRowLds, DT>(p.amode);
-    return pick_row_am<MT, NW, L, kMetaRowGlobal, DT>(p.amode);
+    if constexpr (NW <= 8) return pick_row_am<MT, NW, L, kMetaRowGlobal, DT>(p.amode);
   }
   return nullptr;
 }

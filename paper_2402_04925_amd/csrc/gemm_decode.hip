@@ -58,24 +58,20 @@ __global__ __launch_bounds__(64) void k_gather_prep(const uint16_t* __restrict__
     u4_t v = {0u, 0u, 0u, 0u};
     if (m < M && r < kw) {
       const uint16_t* xr = X + (int64_t)m * ldx;
-      uint32_t c[8];
       if (perm) {
         const u4_t p0 = *(const u4_t*)(perm + r * 8);
         const u4_t p1 = *(const u4_t*)(perm + r * 8 + 4);
+        uint32_t x[8];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          c[e] = min(p0[e], kmax);
-          c[e + 4] = min(p1[e], kmax);
+          x[e] = xr[min(p0[e], kmax)];
+          x[e + 4] = xr[min(p1[e], kmax)];
         }
+        v = u4_t{x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16), x[6] | (x[7] << 16)};
       } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) c[e] = (uint32_t)(r * 8 + e);
+        v = *(const u4_t*)(xr + r * 8);
       }
-      uint32_t x[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) x[e] = xr[c[e]];
-      v = natural ? u4_t{x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16), x[6] | (x[7] << 16)}
-                  : u4_t{x[0] | (x[4] << 16), x[1] | (x[5] << 16), x[2] | (x[6] << 16), x[3] | (x[7] << 16)};
+      if (!natural) v = permute_octet(v);
     }
     *(u4_t*)(Xp + i * 8) = v;
   }
@@ -108,20 +104,23 @@ bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int met
   if (meta == kMetaGroup &&
       (G <= 0 || G % 32 != 0 || !(spg == 1 || spg == 2 || spg == 4 || spg == 8)))
     meta = kMetaRowLds;  // sorted rows of another G: per-row groups floor(k / G)
-  if ((meta != kMetaGroup || mt == 4) && nw > 8) nw = 8;
+  if (((meta != kMetaGroup && K < 4096) || (meta != kMetaGroup ? mt > 1 : mt == 4)) && nw > 8) nw = 8;
   if (meta != kMetaGroup && mt == 4) nw = 4;  // four row tiles of per-row dequant: registers
   if (gated && nw > 8) nw = 8;                 // two weight streams per wave
   // tile metadata in LDS: the per-row act-order kernel only (the ordered
   // kernel's travels with its weight stream)
   int meta_rows = meta == kMetaRowLds ? num_groups : 0;
   const size_t red = (size_t)nw * mt * (gated ? 2 : 1) * 1024;
-  size_t meta_bytes =
-      meta_rows ? align_up(((size_t)meta_rows * kTileN + 1) * 16, 16) : 0;  // + a spare entry
-  if (meta_bytes > kLdsMax - red) {
+  // entries of 4 bytes (gated 8) + a spare one, then two bytes per row of K:
+  // the offset of its group's entries (in 16 bits, so at most 1024 groups)
+  const size_t lds_g_off = align_up(((size_t)meta_rows * kTileN + 1) * (gated ? 8 : 4), 16);
+  size_t meta_bytes = meta_rows ? lds_g_off + (size_t)((K + 127) / 128) * 256 : 0;
+  if (meta_bytes > kLdsMax - red || meta_rows > 1024) {
     meta = kMetaRowGlobal;
     meta_rows = 0;
     meta_bytes = 0;
   }
+  if (meta == kMetaRowGlobal && nw > 8) nw = 8;  // its metadata in registers: 16 waves would spill
   // padded X + the zero entry + a spare entry
   const size_t x_bytes = ((size_t)M * 16 * ((K + 127) / 128) + 2) * 16;
   // the gather's copy of X + spare: row-major, or column-major with four
@@ -199,6 +198,7 @@ bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int met
   p->mt = mt;
   p->spg = spg;
   p->meta_rows = meta_rows;
+  p->lds_g_off = (int)lds_g_off;
   p->lds_x_off = (int)meta_bytes;
   p->lds_xr_off = (int)(meta_bytes + x_bytes);
   size_t need = a_global(am) ? meta_bytes : meta_bytes + x_bytes;  // <= budget when staged
@@ -234,6 +234,7 @@ hipError_t launch_decode(const GemmArgs& a0, const DecodePlan& p, float* part, h
   if (!k) return hipErrorInvalidValue;
   GemmArgs a = a0;
   a.meta_rows = p.meta_rows;
+  a.lds_g_off = p.lds_g_off;
   a.lds_x_off = p.lds_x_off;
   a.lds_xr_off = p.lds_xr_off;
   if (p.lds_bytes > 64 * 1024) {

@@ -171,6 +171,41 @@ __device__ __forceinline__ u4_t dequant_rows(const UnpackConsts<DT>& k, uint32_t
   }
 }
 
+// dequant_rows on metadata entries e[r] = scale bits | (0x6400 | z) << 16:
+// two byte permutes make the zero pair (fp16 1024 + z) and the scale pair of
+// each packed value pair. The nibbles at bits 4 .. 7 land as 1024 + 16 q and
+// one FMA brings them to 1024 + q (64 + q + 960, exact), so that both kinds
+// take the same zero pair.
+template <bool NAT, int DT>
+__device__ __forceinline__ u4_t dequant_entries(const UnpackConsts<DT>& k, uint32_t w, const uint32_t (&e)[8]) {
+  if constexpr (DT == kF16) {
+    constexpr int ra[4] = {0, NAT ? 2 : 1, NAT ? 4 : 2, NAT ? 6 : 3};
+    constexpr int rb[4] = {NAT ? 1 : 4, NAT ? 3 : 5, NAT ? 5 : 6, 7};
+    const uint32_t w8 = w >> 8;
+    const h2_t inv16 = {(_Float16)0.0625f, (_Float16)0.0625f};
+    const h2_t c960 = {(_Float16)960.f, (_Float16)960.f};
+    u4_t r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t ws = i < 2 ? w : w8;
+      h2_t q = as_h2((ws & (i & 1 ? k.hi : k.lo)) | k.magic);
+      if (i & 1) q = __builtin_elementwise_fma(q, inv16, c960);
+      const h2_t z = as_h2(__builtin_amdgcn_perm(e[rb[i]], e[ra[i]], 0x07060302u));
+      const h2_t s = as_h2(__builtin_amdgcn_perm(e[rb[i]], e[ra[i]], 0x05040100u));
+      r[i] = as_u32((q - z) * s);
+    }
+    return r;
+  } else {
+    uint32_t z[8], s[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      z[r] = (e[r] >> 16) & 0x1Fu;
+      s[r] = e[r] & 0xFFFFu;
+    }
+    return dequant_rows<NAT, DT>(k, w, z, s);
+  }
+}
+
 // 8 consecutive fp16 activations x0..x7 -> x0, x4, x1, x5, x2, x6, x3, x7.
 __device__ __forceinline__ u4_t permute_octet(u4_t x) {
   u4_t r;

@@ -75,6 +75,7 @@ struct GemmArgs {
   const uint16_t* sc_up;
   const uint32_t* qz_up;
   int meta_rows;          // metadata rows staged in LDS
+  int lds_g_off;          // kMetaRowLds: byte offset of the rows' entry offsets in LDS
   int lds_x_off;          // byte offset of the staged X in LDS
   int lds_xr_off;         // kALdsGather: byte offset of the LDS copy of X's rows
 };
@@ -91,6 +92,7 @@ struct DecodePlan {
   int tn;       // 16-column tiles per workgroup (ordered kernel: 1 or 2)
   int spg;      // 32-row steps per group (kMetaGroup)
   int meta_rows;
+  int lds_g_off;
   size_t lds_bytes;
   int lds_x_off;
   int lds_xr_off;
