@@ -1116,6 +1116,11 @@ __global__ __launch_bounds__(NW * 64) void k_rowmeta(GemmArgs a) {
     acc[t] = f4_t{0.f, 0.f, 0.f, 0.f};
     accu[t] = f4_t{0.f, 0.f, 0.f, 0.f};
   }
+  // LDS address of column j's entry of group 0: an entry's address is then one
+  // addition of a row's 16-bit offset
+  typedef const __attribute__((address_space(3))) uint32_t* lds_u32_t;
+  typedef const __attribute__((address_space(3))) uint64_t* lds_u64_t;
+  const uint32_t meta_at = (uint32_t)(uintptr_t)(lds_u32_t)(meta + MW * j);
   const uint32_t gmax = (uint32_t)(a.num_groups - 1);
   const int zshift = 4 * (col & 7);
   const uint32_t zoff = (uint32_t)a.zoff;
@@ -1149,13 +1154,13 @@ __global__ __launch_bounds__(NW * 64) void k_rowmeta(GemmArgs a) {
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
           const uint32_t o16 = (r & 1) ? gp[r >> 1] >> 16 : gp[r >> 1] & 0xFFFFu;
-          const unsigned char* p = smem + ((o16 << (MW - 1)) | (uint32_t)(4 * MW * j));
+          const uint32_t at = (o16 << (MW - 1)) + meta_at;
           if constexpr (GATED) {
-            const uint2 v = *(const uint2*)p;
-            e[r] = v.x;
-            eu[r] = v.y;
+            const uint64_t v = *(lds_u64_t)(uintptr_t)at;
+            e[r] = (uint32_t)v;
+            eu[r] = (uint32_t)(v >> 32);
           } else {
-            e[r] = *(const uint32_t*)p;
+            e[r] = *(lds_u32_t)(uintptr_t)at;
           }
         }
         bv = dequant_entries<LAYOUT == TPDQ_LAYOUT_TILED, DT>(kc, wb[u], e);
