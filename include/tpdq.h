@@ -201,12 +201,13 @@ tpdq_status tpdq_pack_tiled(const tpdq_w4* w, int32_t* qweight_out, void* stream
  *    act-order paths need w->g_idx; values outside [0, num_groups) are
  *    clamped into range (no fault; such rows give unspecified results).
  * Y  [M][ldy] output, 8 B aligned, ldy % 4 == 0, ldy >= N.
- * Workspace: at least tpdq_workspace_bytes(1, M, w, NULL) bytes, any content
- * (it holds the gathered X' when the gather cannot be done on chip, and the
- * fp32 split-K partials of the kernels that split K: on large weights, and
- * on weights of 16M elements or more when X is row-major and M > 16). A
- * call with x_perm always needs one; without x_perm, a call that needs none
- * accepts NULL. Calls that overlap in time must not share a workspace.
+ * Workspace: tpdq_workspace_bytes(1, M, w, NULL) bytes, any content (it holds
+ * the gathered X', a copy of X in operand order, fp32 split-K partials, or a
+ * chunk of dequantized weights, as the route takes). A call with x_perm always
+ * needs one, as does one without on weights of 64M elements or more with M > 2
+ * (tiled) and on tiled weights of 16M or more with M > 32, or M > 16 and K >=
+ * N; any other call accepts NULL, or less, and then takes a slower route.
+ * Calls that overlap in time must not share a workspace.
  * Deterministic: the same inputs give bit-identical outputs (split-K
  * partials are added in a fixed order).
  */

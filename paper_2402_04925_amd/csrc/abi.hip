@@ -97,10 +97,10 @@ tpdq_status check_layer(const tpdq_w4* w, const char* name, bool need_gidx, bool
 // 2 bytes per row tile and 128-row block, chunks of 64 rows). The M-tiled
 // kernel uses [X[:, perm] row-major, M x K x 2 bytes, when perm is given]
 // [fp32 split-K partials].
-size_t decode_gather_bytes(int M, int K) {
-  const int mc = std::min(M, kDecodeMaxM);
-  return align_up((size_t)((mc + kTileM - 1) / kTileM) * ((K + 127) / 128) * 4096);
+size_t prepared_bytes(int rows, int K) {
+  return align_up((size_t)((rows + kTileM - 1) / kTileM) * ((K + 127) / 128) * 4096);
 }
+size_t decode_gather_bytes(int M, int K) { return prepared_bytes(std::min(M, kDecodeMaxM), K); }
 
 size_t mtile_gather_bytes(int M, int K, bool perm) { return perm ? align_up((size_t)M * K * 2) : 0; }
 
@@ -109,6 +109,35 @@ size_t mtile_gather_bytes(int M, int K, bool perm) { return perm ? align_up((siz
 // faster is used where the caller's buffer holds it.
 constexpr size_t kBaseWs = 0;
 constexpr size_t kAnyWs = SIZE_MAX;
+
+// Sorted rows in whole 32-row steps: the ordered kernels' group sizes.
+bool step_groups(int G) { return G == 32 || G == 64 || G == 128 || G == 256; }
+
+// The ordered kernel's row groups on up to kRowsMaxM rows of X (a perm needs
+// the prepared operand: where `avail` bytes hold it). Weights of
+// kWideMinWeights or more in the tiled order have the wide and the M-tiled
+// kernel.
+bool rows_route(int M, bool perm, const tpdq_w4* w, int meta, size_t avail) {
+  return meta == kMetaGroup && step_groups(w->group_size) &&
+         !(w->layout == TPDQ_LAYOUT_TILED && (int64_t)w->K * w->N >= kWideMinWeights) &&
+         (!perm || (avail != kBaseWs && avail >= prepared_bytes(std::min(M, kRowsMaxM), w->K)));
+}
+
+// Without a perm, whether the row groups read X from a copy in operand order
+// (a launch of its own, about 2 us) or as it is. us with the copy / without:
+// 2048 x 2048 at M = 64 7.3 / 5.3, 255 12.2 / 9.7; 6144 x 6144 at M = 32 12.0 /
+// 10.9, 64 16.5 / 17.4, 255 40.5 / 47.0; 4096 x 4096 at M = 64 10.7 / 11.5,
+// 160 21.8 / 24.7; 2048 x 8192 11.0 / 9.9, 18.9 / 20.3.
+bool rows_copy(int M, const tpdq_w4* w, size_t avail) {
+  const int64_t least = (int64_t)(M > kDecodeMaxM ? 16 : 24) << 20;
+  return M > 2 * kTileM && (int64_t)w->K * w->N >= least && avail != kBaseWs &&
+         avail >= prepared_bytes(std::min(M, kRowsMaxM), w->K);
+}
+
+// Rows of one launch of the decode kernels.
+int chunk_rows(int M, bool perm, const tpdq_w4* w, int meta, size_t avail) {
+  return M > kDecodeMaxM && rows_route(M, perm, w, meta, avail) ? kRowsMaxM : kDecodeMaxM;
+}
 
 // The M-tiled kernel's plan when it covers the call. With a perm its row
 // gather (k_gather_rows) stages one row of X, K halves, in LDS: past that the
@@ -120,8 +149,16 @@ bool mtile_for(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, int dt
   if (perm && (size_t)w->K * 2 > kLdsMax) return false;
   const size_t gather = mtile_gather_bytes(M, w->K, perm);
   const bool optional = avail != kBaseWs && avail >= gather;
-  return plan_mtile(M, perm ? (int64_t)w->K : ldx, w, meta, dt, gated, optional,
-                    optional ? avail - gather : 0, p);
+  if (!plan_mtile(M, perm ? (int64_t)w->K : ldx, w, meta, dt, gated, optional,
+                  optional ? avail - gather : 0, p))
+    return false;
+  // between 65 and kRowsMaxM rows the ordered kernel's row groups, with X
+  // copied to operand order, may cost less than exact tiles and their partials
+  if (p->exact && !gated && rows_route(M, perm, w, meta, avail)) {
+    const double copy = !perm && rows_copy(M, w, avail) ? 2.5 + (double)M * w->K * 4.0 / 3e6 : 0.0;
+    return p->cost <= rows_cost(M, w->K, w->N, false) + copy;
+  }
+  return true;
 }
 
 // The dequantize-once plan of a call whose rows take their metadata one by one
@@ -131,9 +168,7 @@ bool mtile_for(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, int dt
 // X[:, perm] before it.
 bool dense_for(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, bool gated, size_t avail,
                size_t* gather, DensePlan* p) {
-  const int G = w->group_size;
-  const bool rows = meta == kMetaRowLds ||
-                    (meta == kMetaGroup && G != 32 && G != 64 && G != 128 && G != 256);
+  const bool rows = meta == kMetaRowLds || (meta == kMetaGroup && !step_groups(w->group_size));
   if (!rows || (perm && (size_t)w->K * 2 > kLdsMax)) return false;
   *gather = mtile_gather_bytes(M, w->K, perm);
   return avail > *gather && plan_dense16(M, perm ? (int64_t)w->K : ldx, w, gated, avail - *gather, p);
@@ -145,18 +180,20 @@ bool dense_for(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, bool g
 // any X (*plain); else the prepared operand (*prepared). The workspace of the
 // prepared operand is at least that of the row-major X', so sizes computed
 // without `plain` cover both.
-// Per-row metadata without a perm: the operand is prepared too (a copy in
-// operand order) where `avail` bytes of workspace hold it, from 17 rows on, or
-// 12 on weights of 16M elements: row-major loads touch 16 rows a row apart.
-// 6144 x 6144 act-order GEMM with the copy: M = 64 59.7 -> 38.1 us, M = 32
-// 33.0 -> 24.4, M = 16 23.7 -> 20.8; 2048 x 2048 at M = 16 8.9 -> 8.6, M = 8
-// 7.3 -> 8.5 (the copy is a launch of its own).
+// Without a perm the operand is prepared too (a copy in operand order) where
+// `avail` bytes of workspace hold it and row-major loads, which touch 16 rows
+// a row apart, cost more than the copy's launch: from 17 rows on, and with
+// per-row metadata from 12 on weights of 16M elements. 6144 x 6144 act-order
+// GEMM with the copy: M = 64 59.7 -> 38.1 us, M = 32 33.0 -> 24.4, M = 16 23.7
+// -> 20.8; 2048 x 2048 at M = 16 8.9 -> 8.6, M = 8 7.3 -> 8.5.
 bool decode_plan_for(int mc, bool perm, const tpdq_w4* w, int meta, int dt, DecodePlan* plan,
                      bool* prepared, bool gated, bool* plain, size_t avail) {
   *prepared = false;
   if (plain) *plain = false;
-  if (!perm && meta != kMetaGroup && (mc > 16 || (mc >= 12 && (int64_t)w->K * w->N >= kWideMinWeightsRowMajor)) &&
-      avail != kBaseWs && avail >= decode_gather_bytes(mc, w->K)) {
+  const bool copy = meta == kMetaGroup && step_groups(w->group_size)
+                        ? mc > kTileM && rows_route(mc, false, w, meta, avail) && rows_copy(mc, w, avail)
+                        : mc > kTileM || (mc >= 12 && (int64_t)w->K * w->N >= ((int64_t)16 << 20));
+  if (!perm && copy && avail != kBaseWs && avail >= prepared_bytes(mc, w->K)) {
     *prepared = true;
     return plan_decode(mc, w->K, w->N, w->group_size, w->num_groups, w->layout, meta, kOperandPrepared, dt,
                        plan, gated);
@@ -185,6 +222,21 @@ size_t decode_part_bytes(const DecodePlan& p, int mc, int N) {
   return p.wide && p.ks > 1 ? align_up((size_t)p.ks * mc * N * 4) : 0;
 }
 
+// Row-major X with more than 32 rows, or more than 16 and K >= N, on tiled
+// weights of 16M to 64M elements: the header asks such a call for a workspace
+// of this size (split-K partials; the copy of X that it holds now is smaller).
+size_t rowmajor_need(int M, const tpdq_w4* w, int meta) {
+  const int mc = std::min(M, kDecodeMaxM);
+  const int64_t kn = (int64_t)w->K * w->N;
+  if (meta != kMetaGroup || !step_groups(w->group_size) || w->layout != TPDQ_LAYOUT_TILED ||
+      kn < ((int64_t)16 << 20) || kn >= kWideMinWeights || !(mc > 32 || (mc > 16 && w->K >= w->N)))
+    return 0;
+  const int wgs = ((w->N + kTileN - 1) / kTileN + kWideWaves - 1) / kWideWaves;
+  const int nblk = (w->K + 127) / 128;
+  const int ks = std::max(1, std::min((kWideTargetWgs + wgs - 1) / wgs, std::max(1, nblk / 4)));
+  return ks > 1 ? decode_gather_bytes(M, w->K) + align_up((size_t)ks * mc * w->N * 4) : 0;
+}
+
 // Bytes the call (X with leading dimension ldx, optional perm) uses. Decode:
 // [prepared operand][wide kernel's partials], the partials after the
 // prepared-operand region whenever either is used.
@@ -199,11 +251,12 @@ size_t gemm_ws_need(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, i
     return gather + ep.w_bytes + ep.part_bytes;
   DecodePlan dp;
   bool prepared = false;
-  const int mc = std::min(M, kDecodeMaxM);  // the largest launch
+  const int mc = std::min(M, chunk_rows(M, perm, w, meta, avail));  // the largest launch
+  const size_t legacy = !perm && !gated ? rowmajor_need(M, w, meta) : 0;
   if (!decode_plan_for(mc, perm, w, meta, dt, &dp, &prepared, gated, nullptr, avail))
-    return perm ? decode_gather_bytes(M, w->K) : 0;
+    return perm ? decode_gather_bytes(M, w->K) : legacy;
   const size_t part = decode_part_bytes(dp, mc, w->N);
-  return (prepared || part ? decode_gather_bytes(M, w->K) : 0) + part;
+  return std::max(legacy, (prepared || part ? prepared_bytes(mc, w->K) : 0) + part);
 }
 
 int meta_mode(tpdq_path path) {
@@ -239,8 +292,9 @@ tpdq_status run_gemm(const uint16_t* X, int64_t ldx, int M, const int32_t* perm,
   const size_t avail = ws ? ws_bytes : kBaseWs;
   DensePlan ep;
   size_t gather = 0;
-  const bool mtile = mtile_for(M, ldx, perm != nullptr, w, meta, dt, gated, avail, &mp);
-  if (mtile || dense_for(M, ldx, perm != nullptr, w, meta, gated, avail, &gather, &ep)) {
+  const bool mtile = !io.x_prepared && mtile_for(M, ldx, perm != nullptr, w, meta, dt, gated, avail, &mp);
+  if (mtile ||
+      (!io.x_prepared && dense_for(M, ldx, perm != nullptr, w, meta, gated, avail, &gather, &ep))) {
     // an MFMA GEMM over all rows, the activations gathered first
     const uint16_t* Xa = X;
     int64_t lda = ldx;
@@ -285,8 +339,9 @@ tpdq_status run_gemm(const uint16_t* X, int64_t ldx, int M, const int32_t* perm,
     }
     return TPDQ_OK;
   }
-  for (int m0 = 0; m0 < M; m0 += kDecodeMaxM) {
-    const int mc = std::min(kDecodeMaxM, M - m0);
+  const int chunk = io.x_prepared ? M : chunk_rows(M, perm != nullptr, w, meta, avail);
+  for (int m0 = 0; m0 < M; m0 += chunk) {
+    const int mc = std::min(chunk, M - m0);
     const uint16_t* Xc = X + (int64_t)m0 * ldx;
     int64_t ldc = ldx;
     DecodePlan plan;
@@ -342,7 +397,7 @@ tpdq_status run_gemm(const uint16_t* X, int64_t ldx, int M, const int32_t* perm,
       a.sc_up = (const uint16_t*)io.up->scales;
       a.qz_up = (const uint32_t*)io.up->qzeros;
     }
-    float* part = (float*)(ws + decode_gather_bytes(M, w->K));
+    float* part = (float*)(ws + prepared_bytes(std::min(M, chunk), w->K));
     hipError_t e = launch_decode(a, plan, part, st);
     if (e != hipSuccess) return hip_fail(e, "decode GEMM launch");
   }
@@ -355,23 +410,25 @@ bool is_actorder(tpdq_path p) { return p == TPDQ_PATH_ACTORDER || p == TPDQ_PATH
 // row-major, every load of 16 rows touches 16 rows a row apart (address
 // translation and L1 tag stalls), so GEMM1 then also writes Y1 in GEMM2's
 // operand order (one contiguous KiB per load) into the workspace. Both
-// GEMMs must be single decode launches of the tile kernels (not k_wide, not
-// the M-tiled kernel), and N1 a multiple of 128 (no padding to fill).
+// GEMMs must be single launches of the decode kernels (not k_wide, not the
+// M-tiled kernel) on the routes for `avail` bytes, and N1 a multiple of 128
+// (no padding to fill).
 bool mlp_prepared_y1(int M, int64_t ldx, bool perm, const tpdq_w4* w1, const tpdq_w4* w2, int meta,
-                     int dt, bool gated = false) {
-  if (M > kDecodeMaxM || w1->N % 128 != 0) return false;
+                     int dt, size_t avail, bool gated = false) {
+  if (M > kRowsMaxM || w1->N % 128 != 0) return false;
   MtilePlan mp;
-  if (mtile_for(M, ldx, perm, w1, meta, dt, gated, kBaseWs, &mp) ||
-      mtile_for(M, w1->N, false, w2, meta, dt, false, kBaseWs, &mp))
+  if (mtile_for(M, ldx, perm, w1, meta, dt, gated, avail, &mp) ||
+      mtile_for(M, w1->N, false, w2, meta, dt, false, avail, &mp))
     return false;
+  if (M > kDecodeMaxM) {  // the row groups, X' and Y1' both in the workspace
+    return chunk_rows(M, perm, w1, meta, avail) >= M && chunk_rows(M, false, w2, meta, avail) >= M &&
+           prepared_bytes(M, w1->K) + prepared_bytes(M, w1->N) <= avail;
+  }
   DecodePlan p1, p2;
   bool prepared = false;
   if (!decode_plan_for(M, perm, w1, meta, dt, &p1, &prepared, gated, nullptr, kBaseWs) || p1.wide) return false;
-  // GEMM2 would read row-major Y1 from global memory: through the tile
-  // kernel, or through k_wide only because of the row-major rule (on
-  // weights of kWideMinWeights or more GEMM2 stays on k_wide instead)
-  const bool big2 = (int64_t)w2->K * w2->N >= kWideMinWeights;
-  if (!decode_plan_for(M, false, w2, meta, dt, &p2, &prepared, false, nullptr, kBaseWs) || (p2.wide && big2) ||
+  // GEMM2 would read row-major Y1 from global memory through the tile kernel
+  if (!decode_plan_for(M, false, w2, meta, dt, &p2, &prepared, false, nullptr, kBaseWs) || p2.wide ||
       p2.amode != kAGlobal)
     return false;
   DecodePlan p3;
@@ -386,7 +443,7 @@ size_t y1_offset(int M, int64_t ldx, bool perm, const tpdq_w4* w1, int meta, int
                  size_t ws_bytes, size_t* ws1) {
   const size_t off = gemm_ws_need(M, ldx, perm, w1, meta, dt, gated, ws_bytes);
   *ws1 = ws_bytes;
-  if (off + decode_gather_bytes(M, w1->N) <= ws_bytes) return off;
+  if (off + prepared_bytes(M, w1->N) <= ws_bytes) return off;
   *ws1 = kBaseWs;
   return gemm_ws_need(M, ldx, perm, w1, meta, dt, gated, kBaseWs);
 }
@@ -456,7 +513,7 @@ size_t ws_bound(int op, int32_t M, const tpdq_w4* a, const tpdq_w4* b, size_t av
     if (!b) return 0;
     // GEMM1's region, then Y1 in GEMM2's operand order (mlp_prepared_y1);
     // op 3: GEMM1 is the gated GEMM (a = w_gate)
-    const size_t y1p = M <= kDecodeMaxM ? decode_gather_bytes(M, a->N) : 0;
+    const size_t y1p = M <= (avail == kBaseWs ? kDecodeMaxM : kRowsMaxM) ? prepared_bytes(M, a->N) : 0;
     return std::max(gemm_max(a, true, op == 3) + y1p, gemm_max(b, false, false));
   }
   return 0;
@@ -669,7 +726,7 @@ tpdq_status mlp_shard(const void* X, int64_t ldx, int32_t M, const int32_t* P1, 
   char* ws = (char*)workspace;
   GemmIO io1, io2;
   size_t ws1 = ws_bytes;
-  if (workspace && ws_bytes >= bound && mlp_prepared_y1(M, ldx, !act, w1, w2, meta, dtype)) {
+  if (workspace && ws_bytes >= bound && mlp_prepared_y1(M, ldx, !act, w1, w2, meta, dtype, ws_bytes)) {
     io1.yp = (uint16_t*)(ws + y1_offset(M, ldx, !act, w1, meta, dtype, false, ws_bytes, &ws1));
     io1.yp_natural = w2->layout == TPDQ_LAYOUT_TILED ? 1 : 0;
     io2.x_prepared = true;
@@ -745,7 +802,7 @@ tpdq_status tpdq_gated_mlp_shard(const void* X, int64_t ldx, int32_t M, const in
   GemmIO io1, io2;
   io1.up = w_up;
   size_t ws1 = ws_bytes;
-  if (workspace && ws_bytes >= bound && mlp_prepared_y1(M, ldx, !act, w_gate, w_down, meta, dtype, true)) {
+  if (workspace && ws_bytes >= bound && mlp_prepared_y1(M, ldx, !act, w_gate, w_down, meta, dtype, ws_bytes, true)) {
     io1.yp = (uint16_t*)(ws + y1_offset(M, ldx, !act, w_gate, meta, dtype, true, ws_bytes, &ws1));
     io1.yp_natural = w_down->layout == TPDQ_LAYOUT_TILED ? 1 : 0;
     io2.x_prepared = true;

@@ -342,11 +342,11 @@ __device__ __forceinline__ int64_t prepared_offset(int row, int c, int nsteps, i
 // Sum the NW waves' partial tiles (TN tiles of 16 columns from n0) in LDS
 // and write Y in the element type; with a.Yp, Y is also written in the next
 // GEMM's prepared-operand layout (a.N a multiple of 128: no padding).
-// acc[t][n] of lane l holds rows t*16 + 4*(l/16) + e, column n0 + 16 n +
+// acc[t][n] of lane l holds rows (t0 + t)*16 + 4*(l/16) + e, column n0 + 16 n +
 // l % 16. GATED: tiles 0 and 1 are the gate and up products of the same 16
 // columns, and Y = silu(gate) * up (in fp32, rounded once).
 template <int MT, int NW, int TN, int DT, bool GATED = false>
-__device__ __forceinline__ void reduce_store(const GemmArgs& a, f4_t (&acc)[MT][TN], int n0,
+__device__ __forceinline__ void reduce_store(const GemmArgs& a, f4_t (&acc)[MT][TN], int t0, int n0,
                                              unsigned char* smem) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -373,7 +373,7 @@ __device__ __forceinline__ void reduce_store(const GemmArgs& a, f4_t (&acc)[MT][
         g += red[((w * MT * TN + t * TN + 0) * 4 + e) * 64 + ln];
         u += red[((w * MT * TN + t * TN + 1) * 4 + e) * 64 + ln];
       }
-      const int row = t * kTileM + 4 * (ln >> 4) + e;
+      const int row = (t0 + t) * kTileM + 4 * (ln >> 4) + e;
       const int c = n0 + (ln & 15);
       if (row < a.M && c < a.N) {
         const uint16_t v = float_to_bits<DT>(silu_mul(g, u));
@@ -390,7 +390,7 @@ __device__ __forceinline__ void reduce_store(const GemmArgs& a, f4_t (&acc)[MT][
     float s = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) s += red[((w * MT * TN + tn) * 4 + e) * 64 + ln];
-    const int row = (tn / TN) * kTileM + 4 * (ln >> 4) + e;
+    const int row = (t0 + tn / TN) * kTileM + 4 * (ln >> 4) + e;
     const int c = n0 + (tn % TN) * kTileN + (ln & 15);
     if (row < a.M && c < a.N) {
       const uint16_t v = float_to_bits<DT>(s);
@@ -491,27 +491,28 @@ struct WeightStream {
 // operand order unless they already are, kAGlobalPrep: permuting at the load
 // would make the load be waited for at once).
 // Rows past M read zeros from the resource bound; columns past K are zeroed.
-// kAGlobalPrep reads the prepared operand (k_gather_prep): 16-byte records
+// (the MT row tiles from t0.) kAGlobalPrep reads the prepared operand (k_gather_prep): 16-byte records
 // [row tile t][step s][lane], one contiguous KiB per load instruction, in
 // operand order and zero-padded.
 template <int MT, int AM>
 struct AStream {
   __amdgpu_buffer_rsrc_t rs;
   uint32_t row_off[MT];
-  __device__ __forceinline__ AStream(const GemmArgs& a, int j, int lane) {
+  __device__ __forceinline__ AStream(const GemmArgs& a, int t0, int j, int lane) {
     if constexpr (AM == kAGlobalPrep) {
       const uint32_t nsteps = 4u * (uint32_t)((a.K + 127) >> 7);
-      rs = buffer_rsrc(a.X, (uint32_t)MT * nsteps * 1024u);
+      rs = buffer_rsrc(a.X, (uint32_t)(t0 + MT) * nsteps * 1024u);
       // rows past M hold zeros: skip them (out of range loads cost nothing)
 #pragma unroll
       for (int t = 0; t < MT; ++t)
-        row_off[t] = t * kTileM + j < a.M ? ((uint32_t)t * nsteps * 64u + (uint32_t)lane) * 16u
-                                          : kOutOfRange;
+        row_off[t] = (t0 + t) * kTileM + j < a.M
+                         ? ((uint32_t)(t0 + t) * nsteps * 64u + (uint32_t)lane) * 16u
+                         : kOutOfRange;
     } else {
       rs = buffer_rsrc(a.X, (uint32_t)a.M * (uint32_t)a.ldx * 2u);
 #pragma unroll
       for (int t = 0; t < MT; ++t) {
-        const int row = t * kTileM + j;
+        const int row = (t0 + t) * kTileM + j;
         row_off[t] = row < a.M ? (uint32_t)row * (uint32_t)a.ldx * 2u : kOutOfRange;
       }
     }
@@ -611,8 +612,14 @@ struct ChunkMeta {
 
 // ---------------------------------------------------------------------------
 // Ordered kernel: sorted rows, group of row k = k / G, G = 32 * SPG. A
-// workgroup owns TN 16-column tiles over all of K (TN = 2 halves the
-// activation traffic per column where X is read from global memory). Each
+// workgroup owns TN 16-column tiles and one of a.rgs groups of MT row tiles
+// over all of K. With X read from global memory the bytes per CU bound it: per
+// 128 rows of K a workgroup reads 4 MT KiB of activations from L2 and TN KiB
+// of weights, so more than 16 rows of M are cut into row groups of one or two
+// tiles with up to four column tiles (see plan_rows), neighbouring workgroups
+// sharing their weights in L2. M = 64, one workgroup with all four row tiles
+// and at most two column tiles against row groups: 6144 x 6144 19.2 -> 12.4
+// us, 8192 x 3584 20.2 -> 12.5, 3584 x 8192 13.9 -> 11.1. Each
 // wave owns a run of 128-row blocks and keeps D of them in flight: the loads
 // are issued in the order the blocks are consumed and waited for one block at
 // a time, so the dequant and MFMAs of a block run while later blocks are
@@ -632,14 +639,23 @@ __global__ __launch_bounds__(NW * 64) void k_ordered(GemmArgs a) {
   // fragments (4 * MT registers of 16 bytes per block) ride along. The
   // prepared operand with one row tile keeps four (Llama-70B TP=8 MLP at
   // M = 8: 16.1 -> 14.6 us; at M = 16 equal, 17.1 us), the other global
-  // operands two, or one with four row tiles
-  constexpr int D = AG ? (MT == 4 ? 1 : (AM == kAGlobalPrep && MT == 1 && !GATED ? 4 : 2)) : 4;
+  // operands two
+  constexpr int D = AG ? (AM == kAGlobalPrep && MT == 1 && TN <= 2 && !GATED ? 4 : 2) : 4;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 15;
   const int kq = lane >> 4;
-  const int tile0 = xcd_tile(blockIdx.x, gridDim.x) * (GATED ? 1 : TN);
+  int tg = xcd_tile(blockIdx.x, gridDim.x);
+  int t0 = 0;  // first row tile
+  if constexpr (AG) {
+    if (a.rgs > 1) {  // the division would delay every first load by 0.1 us
+      const int q = tg / a.rgs;
+      t0 = (tg - q * a.rgs) * MT;
+      tg = q;
+    }
+  }
+  const int tile0 = tg * (GATED ? 1 : TN);
   const int ntiles = (a.N + kTileN - 1) / kTileN;
   const int kw = a.K >> 3;
   const int ng = (a.K + 32 * SPG - 1) / (32 * SPG);  // the last group may be partial
@@ -677,7 +693,7 @@ __global__ __launch_bounds__(NW * 64) void k_ordered(GemmArgs a) {
   for (int n = 0; n < TN; ++n)
     wsrc[n].init(GATED && n == 1 ? au : a, tile_of(n), tile_of(n) < ntiles, lane, kq,
                  tile_of(n) * kTileN + j, nblk);
-  const AStream<MT, AM> asrc(a, j, lane);
+  const AStream<MT, AM> asrc(a, t0, j, lane);
   u4_t wb[D][TN];
   u4_t ab[AG ? D : 1][4][MT];
   auto fetch = [&](int b, int slot) {
@@ -801,7 +817,7 @@ __global__ __launch_bounds__(NW * 64) void k_ordered(GemmArgs a) {
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  reduce_store<MT, NW, TN, DT, GATED>(a, acc, tile0 * kTileN, smem);
+  reduce_store<MT, NW, TN, DT, GATED>(a, acc, t0, tile0 * kTileN, smem);
 }
 
 
@@ -1212,38 +1228,40 @@ __global__ __launch_bounds__(NW * 64) void k_rowmeta(GemmArgs a) {
       acc2[t][0] = acc[t];
       acc2[t][1] = accu[t];
     }
-    reduce_store<MT, NW, 2, DT, true>(a, acc2, n0, smem);
+    reduce_store<MT, NW, 2, DT, true>(a, acc2, 0, n0, smem);
   } else {
     f4_t acc1[MT][1];
 #pragma unroll
     for (int t = 0; t < MT; ++t) acc1[t][0] = acc[t];
-    reduce_store<MT, NW, 1, DT>(a, acc1, n0, smem);
+    reduce_store<MT, NW, 1, DT>(a, acc1, 0, n0, smem);
   }
 }
 
 // Kernel selection for a plan (DecodeKernel is declared with DecodePlan).
 // Each dtype is instantiated in its own translation unit.
+template <int MT, int NW, int SPG, int AM, int L, int DT>
+DecodeKernel pick_ordered_tn(int tn) {
+  switch (tn) {
+    case 1: return k_ordered<MT, NW, SPG, AM, L, 1, DT>;
+    case 2: return k_ordered<MT, NW, SPG, AM, L, 2, DT>;
+    case 3: return k_ordered<MT, NW, SPG, AM, L, 3, DT>;
+    case 4: return k_ordered<MT, NW, SPG, AM, L, 4, DT>;
+  }
+  return nullptr;
+}
+
 template <int MT, int NW, int SPG, int L, int DT>
 DecodeKernel pick_ordered_am(int am, int tn) {
-  // plan_decode gives the ordered kernel 4 or 8 waves and one tile with X in
-  // LDS, 4 waves and one or two tiles with X from global memory; only those
-  // are instantiated
-  switch (am) {
-    case kAGlobal:
-      if constexpr (NW == 4)
-        return tn == 2 ? k_ordered<MT, NW, SPG, kAGlobal, L, 2, DT> : k_ordered<MT, NW, SPG, kAGlobal, L, 1, DT>;
-      return nullptr;
-    case kAGlobalPrep:
-      if constexpr (NW == 4)
-        return tn == 2 ? k_ordered<MT, NW, SPG, kAGlobalPrep, L, 2, DT>
-                       : k_ordered<MT, NW, SPG, kAGlobalPrep, L, 1, DT>;
-      return nullptr;
-    case kALds:
-      if constexpr (NW <= 8) return tn == 1 ? k_ordered<MT, NW, SPG, kALds, L, 1, DT> : nullptr;
-      return nullptr;
-    case kALdsGather:
-      if constexpr (NW <= 8) return tn == 1 ? k_ordered<MT, NW, SPG, kALdsGather, L, 1, DT> : nullptr;
-      return nullptr;
+  // plan_decode gives the ordered kernel 4 or 8 waves, one row and one column
+  // tile with X in LDS, 4 waves with X from global memory; only those are
+  // instantiated
+  if constexpr (NW == 4 && MT <= 2) {
+    if (am == kAGlobal) return pick_ordered_tn<MT, NW, SPG, kAGlobal, L, DT>(tn);
+    if (am == kAGlobalPrep) return pick_ordered_tn<MT, NW, SPG, kAGlobalPrep, L, DT>(tn);
+  }
+  if constexpr (NW <= 8 && MT == 1) {
+    if (am == kALds) return tn == 1 ? k_ordered<MT, NW, SPG, kALds, L, 1, DT> : nullptr;
+    if (am == kALdsGather) return tn == 1 ? k_ordered<MT, NW, SPG, kALdsGather, L, 1, DT> : nullptr;
   }
   return nullptr;
 }
@@ -1318,7 +1336,8 @@ DecodeKernel pick_wide(const DecodePlan& p) {
   switch (p.mt) {
     case 1: return prep ? pick_wide_spg<1, 1, true, DT>(p.spg) : pick_wide_spg<1, 1, false, DT>(p.spg);
     case 2: return prep ? pick_wide_spg<2, 1, true, DT>(p.spg) : pick_wide_spg<2, 1, false, DT>(p.spg);
-    case 4: return prep ? pick_wide_spg<4, 1, true, DT>(p.spg) : pick_wide_spg<4, 1, false, DT>(p.spg);
+    // a gather whose row is past the M-tiled kernel's LDS
+    case 4: return prep ? pick_wide_spg<4, 1, true, DT>(p.spg) : nullptr;
   }
   return nullptr;
 }
@@ -1329,15 +1348,13 @@ DecodeKernel pick_wide(const DecodePlan& p) {
 // with a second stream. Instantiated in their own translation units.
 template <int MT, int NW, int SPG, int L, int DT>
 DecodeKernel pick_gated_ordered_am(int am) {
-  switch (am) {
-    case kAGlobal:
-      if constexpr (NW == 4) return k_ordered<MT, NW, SPG, kAGlobal, L, 2, DT, true>;
-      return nullptr;
-    case kAGlobalPrep:
-      if constexpr (NW == 4) return k_ordered<MT, NW, SPG, kAGlobalPrep, L, 2, DT, true>;
-      return nullptr;
-    case kALds: return k_ordered<MT, NW, SPG, kALds, L, 2, DT, true>;
-    case kALdsGather: return k_ordered<MT, NW, SPG, kALdsGather, L, 2, DT, true>;
+  if constexpr (NW == 4 && MT <= 2) {
+    if (am == kAGlobal) return k_ordered<MT, NW, SPG, kAGlobal, L, 2, DT, true>;
+    if (am == kAGlobalPrep) return k_ordered<MT, NW, SPG, kAGlobalPrep, L, 2, DT, true>;
+  }
+  if constexpr (MT == 1) {
+    if (am == kALds) return k_ordered<MT, NW, SPG, kALds, L, 2, DT, true>;
+    if (am == kALdsGather) return k_ordered<MT, NW, SPG, kALdsGather, L, 2, DT, true>;
   }
   return nullptr;
 }

@@ -3,6 +3,8 @@
 // this file instantiates them for fp16, gemm_decode_bf16.hip for bf16.
 #include "decode_kernels.h"
 
+#include <limits.h>
+
 #include <algorithm>
 
 namespace tpdq {
@@ -88,10 +90,41 @@ DecodeKernel decode_kernel(const DecodePlan& p) {
 }
 }  // namespace
 
+// Row groups and column tiles of the ordered kernel with X from global memory
+// and more than one row tile: per 128 rows of K a workgroup reads 4 mt KiB of
+// activations and tn KiB of weights, the latter from HBM (twice the weight),
+// and the workgroups run in rounds of one per CU. Of the best pairs the one
+// with two row tiles. Measured best, M = 64: 6144 x 6144 (2, 3), 3584 x 8192
+// (2, 4), 8192 x 3584 (2, 2) and (1, 4) alike; M = 32: (1, 3), (1, 4) and
+// (2, 2) alike, (1, 2). gated: the two streams of one column tile.
+static int plan_rows(int M, int N, bool gated, int* mt, int* tn) {
+  const int rt = (M + kTileM - 1) / kTileM;
+  const int ntiles = (N + kTileN - 1) / kTileN;
+  int best = INT_MAX;
+  for (int m : {2, 1})
+    for (int n = gated ? 2 : 1; n <= (gated ? 2 : 4); ++n) {
+      const int64_t wgs = (int64_t)((rt + m - 1) / m) * (gated ? ntiles : (ntiles + n - 1) / n);
+      const int cost = (int)((wgs + 255) / 256) * (4 * m + 2 * n);
+      if (cost < best) {
+        best = cost;
+        *mt = m;
+        *tn = n;
+      }
+    }
+  return best;
+}
+
+// 2 us of launch and 0.0134 us per unit of plan_rows and block of 128 rows
+// (6144 x 6144 at M = 64: 14 units, 48 blocks, 11 us)
+double rows_cost(int M, int K, int N, bool gated) {
+  int mt, tn;
+  return 2.0 + 0.0134 * plan_rows(M, N, gated, &mt, &tn) * ((K + 127) / 128);
+}
+
 bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int meta_pref, int operand,
                  int dt, DecodePlan* p, bool gated) {
-  if (M < 1 || M > kDecodeMaxM) return false;
-  const int mt = M <= 16 ? 1 : (M <= 32 ? 2 : 4);
+  if (M < 1 || M > kRowsMaxM) return false;
+  int mt = M <= 16 ? 1 : (M <= 32 ? 2 : 4);
   const int ntiles = (N + kTileN - 1) / kTileN;
   // waves per workgroup (the per-row kernels): about 16 resident waves per
   // CU over the grid; the ordered kernel is set below
@@ -104,6 +137,7 @@ bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int met
   if (meta == kMetaGroup &&
       (G <= 0 || G % 32 != 0 || !(spg == 1 || spg == 2 || spg == 4 || spg == 8)))
     meta = kMetaRowLds;  // sorted rows of another G: per-row groups floor(k / G)
+  if (M > kDecodeMaxM && (meta != kMetaGroup || operand == kOperandGather)) return false;
   if (((meta != kMetaGroup && K < 4096) || (meta != kMetaGroup ? mt > 1 : mt == 4)) && nw > 8) nw = 8;
   if (meta != kMetaGroup && mt == 4) nw = 4;  // four row tiles of per-row dequant: registers
   if (gated && nw > 8) nw = 8;                 // two weight streams per wave
@@ -165,7 +199,8 @@ bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int met
     // global memory, 4 waves, and two tiles per workgroup (half the re-reads
     // of X) from 384 tiles on: Granite-20B TP=4 at M = 16 (384 tiles, 192
     // workgroups) 14.7 -> 9.7 us per GEMM, while the Llama-70B TP=8 GEMM1
-    // (224 tiles) is slower paired (10.5 -> 11.1 us)
+    // (224 tiles) is slower paired (10.5 -> 11.1 us); more than 16 rows as
+    // plan_rows cuts them
     const int nblk = (K + 127) / 128;
     nw = (!a_global(am) && nblk >= 48 && ntiles <= 256) ? 8 : 4;
     if (a_global(am) && ntiles >= 384) tn = 2;
@@ -177,11 +212,15 @@ bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int met
   // the wide kernel when X is read from global memory and the weights are
   // large (the decode kernel re-reads X for every 16 columns): 8 waves over
   // 128 columns share X through LDS, K split until about kWideTargetWgs
-  // workgroups stream
+  // workgroups stream; more than 32 rows of X as it is are the M-tiled kernel's
   p->wide = !gated && meta == kMetaGroup && layout == TPDQ_LAYOUT_TILED && a_global(am) &&
-            ((int64_t)K * N >= kWideMinWeights ||
-             (am == kAGlobal && (mt == 4 || (mt == 2 && K >= N)) &&
-              (int64_t)K * N >= kWideMinWeightsRowMajor));
+            M <= kDecodeMaxM && !(mt == 4 && am == kAGlobal) && (int64_t)K * N >= kWideMinWeights;
+  p->rgs = 1;
+  if (meta == kMetaGroup && a_global(am) && !p->wide && M > kTileM) {
+    plan_rows(M, N, gated, &mt, &tn);
+    p->rgs = ((M + kTileM - 1) / kTileM + mt - 1) / mt;
+    nw = 4;
+  }
   p->ks = 1;
   if (p->wide) {
     const int nblk = (K + 127) / 128;
@@ -233,6 +272,7 @@ hipError_t launch_decode(const GemmArgs& a0, const DecodePlan& p, float* part, h
   DecodeKernel k = decode_kernel(p);
   if (!k) return hipErrorInvalidValue;
   GemmArgs a = a0;
+  a.rgs = p.rgs;
   a.meta_rows = p.meta_rows;
   a.lds_g_off = p.lds_g_off;
   a.lds_x_off = p.lds_x_off;
@@ -243,7 +283,8 @@ hipError_t launch_decode(const GemmArgs& a0, const DecodePlan& p, float* part, h
     if (e != hipSuccess) return e;
   }
   const int ntiles = (a.N + kTileN - 1) / kTileN;
-  const int grid = p.gated ? ntiles : (ntiles + p.tn - 1) / p.tn;  // gated: both streams, one tile
+  // gated: both streams, one tile
+  const int grid = (p.gated ? ntiles : (ntiles + p.tn - 1) / p.tn) * p.rgs;
   hipLaunchKernelGGL(k, dim3(grid), dim3(p.nw * 64), p.lds_bytes, s, a);
   return hipGetLastError();
 }

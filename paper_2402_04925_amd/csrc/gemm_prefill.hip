@@ -526,6 +526,7 @@ bool plan_mtile(int M, int64_t ldx, const tpdq_w4* w, int meta, int dt, bool gat
       const double cost = mtile_cost(M, N, nblk, rt, ks, gated, exact, dt);
       if (cost < 0.98 * best) {
         best = cost;
+        c.cost = cost;
         *p = c;
       }
     }

@@ -21,6 +21,9 @@ inline size_t align_up(size_t x, size_t a = kWsAlign) { return (x + a - 1) / a *
 constexpr int kTileN = 16;
 constexpr int kTileM = 16;
 constexpr int kDecodeMaxM = 64;
+// Rows one launch of the ordered kernel takes with a prepared operand (its row
+// groups); other launches of the decode kernels take kDecodeMaxM
+constexpr int kRowsMaxM = 256;
 // Largest LDS a decode workgroup may use (gfx950 has 160 KB per CU).
 constexpr size_t kLdsMax = 160 * 1024;
 
@@ -74,6 +77,7 @@ struct GemmArgs {
   const uint32_t* qw_up;
   const uint16_t* sc_up;
   const uint32_t* qz_up;
+  int rgs;                // k_ordered: row groups of the launch
   int meta_rows;          // metadata rows staged in LDS
   int lds_g_off;          // kMetaRowLds: byte offset of the rows' entry offsets in LDS
   int lds_x_off;          // byte offset of the staged X in LDS
@@ -88,8 +92,9 @@ struct DecodePlan {
   int meta;     // MetaMode
   int amode;    // AMode
   int nw;       // waves per workgroup
-  int mt;       // row tiles (1, 2, 4)
-  int tn;       // 16-column tiles per workgroup (ordered kernel: 1 or 2)
+  int mt;       // row tiles per workgroup (1, 2, 4)
+  int rgs;      // row groups of mt tiles (ordered kernel, X from global memory)
+  int tn;       // 16-column tiles per workgroup (ordered kernel: 1 to 4)
   int spg;      // 32-row steps per group (kMetaGroup)
   int meta_rows;
   int lds_g_off;
@@ -104,11 +109,6 @@ struct DecodePlan {
 // kWideTargetWgs workgroups stream.
 constexpr int kWideWaves = 8;
 constexpr int64_t kWideMinWeights = (int64_t)64 << 20;
-// ... and from 16M elements when X is row-major with four row tiles
-// (M > 32), or two with K >= N: the tile kernel's loads of row-major X then
-// touch 16 rows a row apart per instruction, which the wide kernel's staging
-// avoids (with two row tiles and K < N the tile kernel stays faster)
-constexpr int64_t kWideMinWeightsRowMajor = (int64_t)16 << 20;
 constexpr int kWideTargetWgs = 200;
 
 // The in-LDS gather of X[:, perm] is planned on grids of at most this many
@@ -156,10 +156,13 @@ struct MtilePlan {
   int rt, nw, st, ks;  // row tiles and waves per workgroup, LDS stages, K splits
   bool exact;          // q - z in the MFMAs, scales in fp32 (else weights rounded)
   bool gated;          // Y = silu(X W) * (X W_up)
+  double cost;         // exact plans: microseconds by the planner's model
 };
 // optional: also the plans that only serve as a faster route than another one
 // (exact, or a K split at prefill sizes), with partials of at most part_budget
 // bytes
+// Microseconds of the ordered kernel's row groups at M rows on this weight
+double rows_cost(int M, int K, int N, bool gated);
 bool plan_mtile(int M, int64_t ldx, const tpdq_w4* w, int meta, int dt, bool gated, bool optional,
                 size_t part_budget, MtilePlan* p);
 // workspace bytes of the fp32 partials (0 when ks == 1)
