@@ -679,7 +679,14 @@ __global__ __launch_bounds__(NW * 64) void k_ordered(GemmArgs a) {
   //    (the scheduling barriers keep that issue order: loads complete in
   //    order, so a load moved behind the weights would be waited for last)
   XStage<NT, AM == kALdsGather, LAYOUT> xst;
-  if constexpr (!AG) xst.load(a, tid);
+  if constexpr (!AG) {
+    xst.load(a, tid);
+    // a CU returns loads in order over all its waves: with several rows of X
+    // to stage, no wave's weights go out before every wave's X (8192 x 3584 at
+    // M = 4 6.04 -> 5.81 us; at M = 1 nothing to gain)
+    __builtin_amdgcn_sched_barrier(0);
+    if (a.M > 2) __builtin_amdgcn_s_barrier();
+  }
   __builtin_amdgcn_sched_barrier(0);
   ChunkMeta<SPG, DT> cm[TN];
 #pragma unroll
@@ -799,21 +806,38 @@ __global__ __launch_bounds__(NW * 64) void k_ordered(GemmArgs a) {
     }
   };
 
-  // Every load is unconditional (a block or group past the run loads zeros
-  // for free), so that each use waits for exactly what it needs: a load
-  // behind a branch makes the wait counts fall back to waiting for all.
-  for (int c = b0; c < b1; c += 4) {
+  // Every load is unconditional (a block or group past the run loads zeros),
+  // so that each use waits for exactly what it needs: a load behind a branch
+  // makes the wait counts fall back to waiting for all. The last chunk is a
+  // copy of its own that loads no block past the run: loads of zeros move no
+  // data, but each takes its turn on the CU's address path (D blocks of them
+  // per wave: 0.1 to 0.6 us a kernel; 3584 x 8192 at M = 8 6.38 -> 5.83 us,
+  // 8192 x 3584 at M = 1 5.50 -> 5.36, 6144 x 6144 at M = 64 16.4 -> 15.3).
+  // GPTQ-layout weights (four address operations a block) have no registers
+  // left for the second copy: there the loop runs to the end.
+  constexpr bool PEEL = LAYOUT == TPDQ_LAYOUT_TILED;
+  int c = b0;
+  for (; PEEL ? c + 4 < b1 : c < b1; c += 4) {
 #pragma unroll
     for (int n = 0; n < TN; ++n) {
       cm[n].decode();
-      cm[n].load((4 * (c + 4)) / SPG, c + 4 < b1, ng, kq);
+      cm[n].load((4 * (c + 4)) / SPG, PEEL || c + 4 < b1, ng, kq);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int b = c + i;
-      if (b < b1) block(c, i, wb[i % D], ab[AG ? i % D : 0]);
-      fetch(b + D, i % D);
+      if (PEEL || c + i < b1) block(c, i, wb[i % D], ab[AG ? i % D : 0]);
+      fetch(c + i + D, i % D);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  if (PEEL && c < b1) {
+#pragma unroll
+    for (int n = 0; n < TN; ++n) cm[n].decode();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (c + i < b1) block(c, i, wb[i % D], ab[AG ? i % D : 0]);
+      if (i + D < 4) fetch(c + i + D, i % D);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -1241,12 +1265,11 @@ __global__ __launch_bounds__(NW * 64) void k_rowmeta(GemmArgs a) {
 // Each dtype is instantiated in its own translation unit.
 template <int MT, int NW, int SPG, int AM, int L, int DT>
 DecodeKernel pick_ordered_tn(int tn) {
-  switch (tn) {
-    case 1: return k_ordered<MT, NW, SPG, AM, L, 1, DT>;
-    case 2: return k_ordered<MT, NW, SPG, AM, L, 2, DT>;
-    case 3: return k_ordered<MT, NW, SPG, AM, L, 3, DT>;
-    case 4: return k_ordered<MT, NW, SPG, AM, L, 4, DT>;
-  }
+  constexpr int MAX = rows_max_tn(L, SPG, MT);
+  if constexpr (MAX >= 1) if (tn == 1) return k_ordered<MT, NW, SPG, AM, L, 1, DT>;
+  if constexpr (MAX >= 2) if (tn == 2) return k_ordered<MT, NW, SPG, AM, L, 2, DT>;
+  if constexpr (MAX >= 3) if (tn == 3) return k_ordered<MT, NW, SPG, AM, L, 3, DT>;
+  if constexpr (MAX >= 4) if (tn == 4) return k_ordered<MT, NW, SPG, AM, L, 4, DT>;
   return nullptr;
 }
 
@@ -1348,7 +1371,7 @@ DecodeKernel pick_wide(const DecodePlan& p) {
 // with a second stream. Instantiated in their own translation units.
 template <int MT, int NW, int SPG, int L, int DT>
 DecodeKernel pick_gated_ordered_am(int am) {
-  if constexpr (NW == 4 && MT <= 2) {
+  if constexpr (NW == 4 && MT <= 2 && rows_max_tn(L, SPG, MT) >= 2) {
     if (am == kAGlobal) return k_ordered<MT, NW, SPG, kAGlobal, L, 2, DT, true>;
     if (am == kAGlobalPrep) return k_ordered<MT, NW, SPG, kAGlobalPrep, L, 2, DT, true>;
   }

@@ -97,12 +97,12 @@ DecodeKernel decode_kernel(const DecodePlan& p) {
 // with two row tiles. Measured best, M = 64: 6144 x 6144 (2, 3), 3584 x 8192
 // (2, 4), 8192 x 3584 (2, 2) and (1, 4) alike; M = 32: (1, 3), (1, 4) and
 // (2, 2) alike, (1, 2). gated: the two streams of one column tile.
-static int plan_rows(int M, int N, bool gated, int* mt, int* tn) {
+static int plan_rows(int M, int N, int layout, int spg, bool gated, int* mt, int* tn) {
   const int rt = (M + kTileM - 1) / kTileM;
   const int ntiles = (N + kTileN - 1) / kTileN;
   int best = INT_MAX;
   for (int m : {2, 1})
-    for (int n = gated ? 2 : 1; n <= (gated ? 2 : 4); ++n) {
+    for (int n = gated ? 2 : 1; n <= std::min(gated ? 2 : 4, rows_max_tn(layout, spg, m)); ++n) {
       const int64_t wgs = (int64_t)((rt + m - 1) / m) * (gated ? ntiles : (ntiles + n - 1) / n);
       const int cost = (int)((wgs + 255) / 256) * (4 * m + 2 * n);
       if (cost < best) {
@@ -116,9 +116,9 @@ static int plan_rows(int M, int N, bool gated, int* mt, int* tn) {
 
 // 2 us of launch and 0.0134 us per unit of plan_rows and block of 128 rows
 // (6144 x 6144 at M = 64: 14 units, 48 blocks, 11 us)
-double rows_cost(int M, int K, int N, bool gated) {
+double rows_cost(int M, const tpdq_w4* w) {
   int mt, tn;
-  return 2.0 + 0.0134 * plan_rows(M, N, gated, &mt, &tn) * ((K + 127) / 128);
+  return 2.0 + 0.0134 * plan_rows(M, w->N, w->layout, w->group_size / 32, false, &mt, &tn) * ((w->K + 127) / 128);
 }
 
 bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int meta_pref, int operand,
@@ -217,7 +217,7 @@ bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int met
             M <= kDecodeMaxM && !(mt == 4 && am == kAGlobal) && (int64_t)K * N >= kWideMinWeights;
   p->rgs = 1;
   if (meta == kMetaGroup && a_global(am) && !p->wide && M > kTileM) {
-    plan_rows(M, N, gated, &mt, &tn);
+    plan_rows(M, N, layout, spg, gated, &mt, &tn);
     p->rgs = ((M + kTileM - 1) / kTileM + mt - 1) / mt;
     nw = 4;
   }

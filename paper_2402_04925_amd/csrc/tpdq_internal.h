@@ -111,6 +111,16 @@ constexpr int kWideWaves = 8;
 constexpr int64_t kWideMinWeights = (int64_t)64 << 20;
 constexpr int kWideTargetWgs = 200;
 
+// Column tiles per workgroup that the ordered kernel's registers hold beside mt
+// row tiles read from global memory (0: not that many row tiles): GPTQ-layout
+// weights, and the metadata of groups of 32 and 64 (spg 1, 2), take more
+constexpr int rows_max_tn(int layout, int spg, int mt) {
+  if (layout == TPDQ_LAYOUT_TILED) return spg == 1 && mt == 2 ? 3 : 4;
+  if (spg == 1) return mt == 1 ? 2 : 0;
+  if (spg == 2) return mt == 1 ? 4 : 2;
+  return 4;
+}
+
 // The in-LDS gather of X[:, perm] is planned on grids of at most this many
 // 16-column tiles; on larger ones (the unsharded Llama-70B GEMM1: 1792 tiles,
 // each workgroup loading the 32 KiB permutation and X) the caller gathers X'
@@ -162,7 +172,7 @@ struct MtilePlan {
 // (exact, or a K split at prefill sizes), with partials of at most part_budget
 // bytes
 // Microseconds of the ordered kernel's row groups at M rows on this weight
-double rows_cost(int M, int K, int N, bool gated);
+double rows_cost(int M, const tpdq_w4* w);
 bool plan_mtile(int M, int64_t ldx, const tpdq_w4* w, int meta, int dt, bool gated, bool optional,
                 size_t part_budget, MtilePlan* p);
 // workspace bytes of the fp32 partials (0 when ks == 1)
