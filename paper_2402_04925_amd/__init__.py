@@ -24,9 +24,15 @@ __all__ = [
 ]
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def version() -> str:
@@ -38,8 +44,13 @@ def _ptr(t) -> Optional[int]:
 
 
 def _stream_handle(device) -> int:
+    """The device's current stream. Asked for as a raw handle where torch offers
+    that: building a Stream object for it takes 2 of a small call's 13 us."""
     torch = _torch()
-    return torch.cuda.current_stream(device).cuda_stream
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return raw(torch.cuda.current_device() if device.index is None else device.index)
 
 
 def _dtype_code(dt) -> int:
@@ -121,6 +132,22 @@ class QuantWeight:
 
     def c_struct(self) -> _abi.W4:
         torch = _torch()
+        q, s, z, g = self.qweight, self.scales, self.qzeros, self.g_idx
+        # every condition of the loops below in one expression (a call makes one
+        # to three of these); they say which one does not hold
+        i32, dev = torch.int32, q.device
+        if not (q.dtype is i32 and z.dtype is i32 and (s.dtype is torch.float16 or s.dtype is torch.bfloat16)
+                and s.device == dev and z.device == dev
+                and q.stride(1) == 1 and s.stride(1) == 1 and z.stride(1) == 1
+                and (g is None or (g.dtype is i32 and g.device == dev and g.is_contiguous()))):
+            self._check_tensors()
+        # positional, in the field order of the C struct
+        return _abi.W4(q.data_ptr(), q.stride(0), s.data_ptr(), s.stride(0), z.data_ptr(), z.stride(0),
+                       None if g is None else g.data_ptr(), self.K, self.N, self.G, self.num_groups,
+                       self.layout, self.zero_offset)
+
+    def _check_tensors(self):
+        torch = _torch()
         for name in ("qweight", "scales", "qzeros", "g_idx"):
             t = getattr(self, name)
             if t is None:
@@ -136,12 +163,6 @@ class QuantWeight:
                 raise ValueError(f"{name} must have unit column stride")
         if self.g_idx is not None and not self.g_idx.is_contiguous():
             raise ValueError("g_idx must be contiguous")
-        return _abi.W4(
-            qweight=_ptr(self.qweight), ld_q=self.qweight.stride(0),
-            scales=_ptr(self.scales), ld_s=self.scales.stride(0),
-            qzeros=_ptr(self.qzeros), ld_z=self.qzeros.stride(0),
-            g_idx=_ptr(self.g_idx), K=self.K, N=self.N, group_size=self.G,
-            num_groups=self.num_groups, layout=self.layout, zero_offset=self.zero_offset)
 
     @property
     def device(self):

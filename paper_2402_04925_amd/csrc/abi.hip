@@ -542,7 +542,13 @@ const char* tpdq_status_string(tpdq_status s) {
 const char* tpdq_last_error(void) { return g_last_error.c_str(); }
 
 size_t tpdq_workspace_bytes(int op, int32_t M, const tpdq_w4* a, const tpdq_w4* b) {
-  return std::max(ws_bound(op, M, a, b, kBaseWs), ws_bound(op, M, a, b, kAnyWs));
+  const size_t base = ws_bound(op, M, a, b, kBaseWs);
+  // up to one decode launch's rows the faster routes add only the copy of X
+  // (or Y1) in operand order, the size of the gather that op 1 and the first
+  // GEMM count already
+  if (M >= 1 && M <= kDecodeMaxM)
+    return base && (op == 2 || op == 3) ? std::max(base, decode_gather_bytes(M, b->K)) : base;
+  return std::max(base, ws_bound(op, M, a, b, kAnyWs));
 }
 
 tpdq_status tpdq_reorder(const tpdq_w4* w1, const tpdq_w4* w2, int32_t* P1, int32_t* g1_sorted,
