@@ -154,7 +154,7 @@ bool mtile_for(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, int dt
     return false;
   // between 65 and kRowsMaxM rows the ordered kernel's row groups, with X
   // copied to operand order, may cost less than exact tiles and their partials
-  if (p->exact && !gated && rows_route(M, perm, w, meta, avail)) {
+  if (M < kPrefillMinM && p->exact && !gated && rows_route(M, perm, w, meta, avail)) {
     const double copy = !perm && rows_copy(M, w, avail) ? 2.5 + (double)M * w->K * 4.0 / 3e6 : 0.0;
     return p->cost <= rows_cost(M, w) + copy;
   }

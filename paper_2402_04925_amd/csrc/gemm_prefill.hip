@@ -26,9 +26,10 @@
 // Dequantizing to fp16 before the MFMA rounds each weight once (relative
 // error 2^-12). With bf16 activations the weight is formed in fp32 and rounded
 // once to bf16 (relative error 2^-9), about four times the VALU work of fp16.
-// The exact variants (see k_prefill) keep q - z in the MFMAs and scale in fp32
-// as the decode kernels do, on 64-row tiles: they serve what would otherwise
-// run in decode launches of 64 rows. Gated Llama-70B TP=8 MLP at M = 1000,
+// The 64-row tiles (EXACT, see k_prefill) keep q - z in the MFMAs and scale in
+// fp32 as the decode kernels do, which costs them nothing (6144 x 6144 at M =
+// 512: 94.5 us, rounded 88.7 us; bf16 faster than rounded): they also serve
+// what would otherwise run in decode launches of 64 rows. Gated Llama-70B TP=8 MLP at M = 1000,
 // bf16: 514 -> 222 us (gate and up in one launch at 0.9 PFLOP/s).
 #include "kernels_common.h"
 
@@ -80,7 +81,7 @@ __device__ __forceinline__ u4_t dequant_scaled_bf16(const UnpackConsts<kBF16>& k
 // 256 registers per lane, with the accumulators in the architectural VGPRs
 // (no accumulator copies between loop iterations).
 //
-// EXACT: the MFMAs take q - z (bf16: 128 + q), exact in the element type, into
+// EXACT (64-row tiles; the 128-row ones round): the MFMAs take q - z (bf16: 128 + q), exact in the element type, into
 // a second set of accumulators, and every group closes with its scale in fp32
 // (bf16: and its zero, against the group's sum of X from one more MFMA per row
 // tile), as the decode kernels do: no weight is rounded. Twice the
@@ -454,12 +455,12 @@ __global__ __launch_bounds__(256) void k_gather_rows(const uint16_t* __restrict_
 // per CU, each over nblk / ks blocks of 128 rows; split partials are written
 // once and read once by the reduce. Per block and round, measured on 6144 x
 // 6144, 8192 x 3584 and 3584 x 8192 at M = 300 to 1500: 128 x 512 tiles 2.8 us
-// (bf16 3.2), 64 x 512 tiles 1.9 us (bf16 2.5 rounded, 2.9 exact), about 4 us
-// of prologue and epilogue; partials at 4.5 TB/s plus a 4 us launch.
-static double mtile_cost(int M, int N, int nblk, int rt, int ks, bool gated, bool exact, int dt) {
+// (bf16 3.2), 64 x 512 tiles 1.9 us (bf16 2.5), about 4 us of prologue and
+// epilogue; partials at 4.5 TB/s plus a 4 us launch.
+static double mtile_cost(int M, int N, int nblk, int rt, int ks, bool gated, int dt) {
   const int bn = gated ? 256 : 512;
   const int64_t wgs = (int64_t)((M + 16 * rt - 1) / (16 * rt)) * ((N + bn - 1) / bn) * ks;
-  const double tb = dt == kBF16 ? (rt == 8 ? 3.2 : (exact ? 2.9 : 2.5)) : (rt == 8 ? 2.8 : 1.9);
+  const double tb = dt == kBF16 ? (rt == 8 ? 3.2 : 2.5) : (rt == 8 ? 2.8 : 1.9);
   const double rounds = (double)((wgs + kMtileSlots - 1) / kMtileSlots);
   const double part = ks > 1 ? 4.0 + (double)ks * M * N * (gated ? 16.0 : 8.0) / 4.5e6 : 0.0;
   return rounds * (4.0 + tb * ((nblk + ks - 1) / ks)) + part;
@@ -496,15 +497,28 @@ bool plan_mtile(int M, int64_t ldx, const tpdq_w4* w, int meta, int dt, bool gat
     // share one copy of the activations); more splits than fit one round are
     // slower (8 waves in 320 slots: GEMM1 280 workgroups, 144 us), and so is
     // one wave per SIMD
-    q.rt = 4;
-    const int tiles = ((M + 63) / 64) * ((N + 511) / 512);
-    q.ks = std::max(1, std::min(kMtileSlots / tiles, nblk / 4));
-    if ((int64_t)q.ks * M * N * 4 >= lim) q.ks = 1;
-    *p = q;
+    auto cut = [&](int rt) {
+      MtilePlan c = q;
+      const int tiles = ((M + 16 * rt - 1) / (16 * rt)) * ((N + 511) / 512);
+      c.rt = rt;
+      c.exact = rt == 4;
+      c.ks = std::max(1, std::min(kMtileSlots / tiles, nblk / 4));
+      if ((int64_t)c.ks * M * N * 4 >= lim) c.ks = 1;
+      return c;
+    };
+    *p = cut(4);
+    // more than one 64-row tile: 128-row tiles halve the activations' share of
+    // a CU's bytes, for twice the partials (8192 x 28672 and 28672 x 8192 at M
+    // = 128: 84.8 and 81.9 us -> 77.1 and 76.7)
+    if (M > 64 && optional) {
+      const MtilePlan c = cut(8);
+      if (mtile_part_bytes(c, M, N) <= part_budget) *p = c;
+    }
     return true;
   }
   // the gated product and smaller weights below prefill sizes keep their
-  // weights exact, as the decode kernels that otherwise run them do
+  // weights exact (64-row tiles), as the decode kernels that otherwise run
+  // them do
   const bool exact = gated || M < kPrefillMinM;
   if (exact && (!optional || M <= kDecodeMaxM)) return false;
   // 128 x 512 tiles over the whole K, or 64 x 512 ones, or either with K
@@ -519,11 +533,11 @@ bool plan_mtile(int M, int64_t ldx, const tpdq_w4* w, int meta, int dt, bool gat
       MtilePlan c = q;
       c.rt = rt;
       c.ks = ks;
-      c.exact = exact;
+      c.exact = rt == 4;
       if (ks > 1 && (!optional || mtile_part_bytes(c, M, N) > part_budget ||
                      (int64_t)ks * M * N * (gated ? 8 : 4) >= lim))
         break;
-      const double cost = mtile_cost(M, N, nblk, rt, ks, gated, exact, dt);
+      const double cost = mtile_cost(M, N, nblk, rt, ks, gated, dt);
       if (cost < 0.98 * best) {
         best = cost;
         c.cost = cost;
@@ -562,11 +576,10 @@ hipError_t launch_mtile_t(const GemmArgs& a, int ks, hipStream_t s) {
 template <int DT>
 hipError_t launch_mtile_dt(const GemmArgs& a, const MtilePlan& p, hipStream_t s) {
   if (p.nw != 8 || p.st != 2) return hipErrorInvalidValue;
-  if (p.gated) return p.rt == 4 && p.exact ? launch_mtile_t<4, DT, true, true>(a, p.ks, s) : hipErrorInvalidValue;
-  if (p.rt == 4)
-    return p.exact ? launch_mtile_t<4, DT, true, false>(a, p.ks, s)
-                   : launch_mtile_t<4, DT, false, false>(a, p.ks, s);
-  return p.rt == 8 && !p.exact ? launch_mtile_t<8, DT, false, false>(a, p.ks, s) : hipErrorInvalidValue;
+  if (p.rt == 4 && p.exact)
+    return p.gated ? launch_mtile_t<4, DT, true, true>(a, p.ks, s) : launch_mtile_t<4, DT, true, false>(a, p.ks, s);
+  return p.rt == 8 && !p.exact && !p.gated ? launch_mtile_t<8, DT, false, false>(a, p.ks, s)
+                                           : hipErrorInvalidValue;
 }
 
 hipError_t launch_mtile(const GemmArgs& a0, const MtilePlan& p, float* part, hipStream_t s) {
