@@ -26,7 +26,7 @@
 // Dequantizing to fp16 before the MFMA rounds each weight once (relative
 // error 2^-12). With bf16 activations the weight is formed in fp32 and rounded
 // once to bf16 (relative error 2^-9), about four times the VALU work of fp16.
-// The 64-row tiles (EXACT, see k_prefill) keep q - z in the MFMAs and scale in
+// Most 64-row tiles (EXACT, see k_prefill) keep q - z in the MFMAs and scale in
 // fp32 as the decode kernels do, which costs them nothing (6144 x 6144 at M =
 // 512: 94.5 us, rounded 88.7 us; bf16 faster than rounded): they also serve
 // what would otherwise run in decode launches of 64 rows. Gated Llama-70B TP=8 MLP at M = 1000,
@@ -81,7 +81,8 @@ __device__ __forceinline__ u4_t dequant_scaled_bf16(const UnpackConsts<kBF16>& k
 // 256 registers per lane, with the accumulators in the architectural VGPRs
 // (no accumulator copies between loop iterations).
 //
-// EXACT (64-row tiles; the 128-row ones round): the MFMAs take q - z (bf16: 128 + q), exact in the element type, into
+// EXACT (64-row tiles; the 128-row ones round, and 64-row ones of groups of 32
+// and 64 on large weights): the MFMAs take q - z (bf16: 128 + q), exact in the element type, into
 // a second set of accumulators, and every group closes with its scale in fp32
 // (bf16: and its zero, against the group's sum of X from one more MFMA per row
 // tile), as the decode kernels do: no weight is rounded. Twice the
@@ -232,9 +233,6 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   f4_t xsum[EXACT && DT == kBF16 ? RT : 1];
   const f4_t fz = {0.f, 0.f, 0.f, 0.f};
   const u4_t ones = {kBf16OnePair, kBf16OnePair, kBf16OnePair, kBf16OnePair};
-  float sf[kPWT], zs[kPWT];  // bf16: the open group's scale and zero term
-  uint32_t z1024[kPWT], z64[kPWT], s2[kPWT];
-
   // block in stage st; the loads of block bn go out one after each column
   // tile's MFMAs, into stage sn
   auto compute = [&](int b, int st, int bnext, int sn) {
@@ -244,6 +242,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     u4_t w[kPWT];
 #pragma unroll
     for (int i = 0; i < kPWT; ++i) w[i] = wb[i * 64 + lane];
+    uint32_t z1024[kPWT], z64[kPWT], s2[kPWT];
+    float sf[kPWT], zs[kPWT];  // bf16, rounded weights
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const bool open = SPG >= 4 ? u == 0 : (u % SPG) == 0;
@@ -496,12 +496,14 @@ bool plan_mtile(int M, int64_t ldx, const tpdq_w4* w, int meta, int dt, bool gat
     // in 512 slots (two per CU), 106.3 us here (GEMM2 52.4 -> 48.9 us: 8 waves
     // share one copy of the activations); more splits than fit one round are
     // slower (8 waves in 320 slots: GEMM1 280 workgroups, 144 us), and so is
-    // one wave per SIMD
+    // one wave per SIMD. Groups of 32 and 64 close four times and twice a block
+    // and keep rounded weights here (8192 x 28672 at M = 64, exact / rounded:
+    // G = 32 63.1 / 60.3 us, G = 64 55.4 / 54.3, G = 128 49.3 / 51.7)
     auto cut = [&](int rt) {
       MtilePlan c = q;
       const int tiles = ((M + 16 * rt - 1) / (16 * rt)) * ((N + 511) / 512);
       c.rt = rt;
-      c.exact = rt == 4;
+      c.exact = rt == 4 && spg > 2;
       c.ks = std::max(1, std::min(kMtileSlots / tiles, nblk / 4));
       if ((int64_t)c.ks * M * N * 4 >= lim) c.ks = 1;
       return c;
@@ -552,6 +554,16 @@ size_t mtile_part_bytes(const MtilePlan& p, int M, int N) {
   return p.ks > 1 ? align_up((size_t)p.ks * M * N * (p.gated ? 8 : 4)) : 0;
 }
 
+hipError_t launch_mtile_k(void (*k)(GemmArgs), int rt, bool gated, const GemmArgs& a, int ks, hipStream_t s) {
+  const int lds = 2 * pf_stage(rt, 8, gated);
+  hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (e != hipSuccess) return e;
+  const int bn = gated ? 256 : 512;
+  const int grid = ((a.M + 16 * rt - 1) / (16 * rt)) * ((a.N + bn - 1) / bn) * ks;
+  hipLaunchKernelGGL(k, dim3(grid), dim3(512), lds, s, a);
+  return hipGetLastError();
+}
+
 template <int RT, int DT, bool EXACT, bool GATED>
 hipError_t launch_mtile_t(const GemmArgs& a, int ks, hipStream_t s) {
   constexpr int NW = 8, ST = 2;
@@ -563,20 +575,19 @@ hipError_t launch_mtile_t(const GemmArgs& a, int ks, hipStream_t s) {
     case 4: k = k_prefill<4, NW, ST, RT, DT, EXACT, GATED>; break;
     case 8: k = k_prefill<8, NW, ST, RT, DT, EXACT, GATED>; break;
   }
-  if (!k) return hipErrorInvalidValue;
-  const int lds = ST * pf_stage(RT, NW, GATED);
-  hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  if (e != hipSuccess) return e;
-  const int bn = (GATED ? 32 : 64) * NW;
-  const int grid = ((a.M + 16 * RT - 1) / (16 * RT)) * ((a.N + bn - 1) / bn) * ks;
-  hipLaunchKernelGGL(k, dim3(grid), dim3(NW * 64), lds, s, a);
-  return hipGetLastError();
+  return k ? launch_mtile_k(k, RT, GATED, a, ks, s) : hipErrorInvalidValue;
 }
 
 template <int DT>
 hipError_t launch_mtile_dt(const GemmArgs& a, const MtilePlan& p, hipStream_t s) {
   if (p.nw != 8 || p.st != 2) return hipErrorInvalidValue;
-  if (p.rt == 4 && p.exact)
+  if (p.rt == 4 && !p.exact) {  // groups of 32 and 64 only (plan_mtile)
+    if (p.gated) return hipErrorInvalidValue;
+    if (a.G == 32) return launch_mtile_k(k_prefill<1, 8, 2, 4, DT, false, false>, 4, false, a, p.ks, s);
+    return a.G == 64 ? launch_mtile_k(k_prefill<2, 8, 2, 4, DT, false, false>, 4, false, a, p.ks, s)
+                     : hipErrorInvalidValue;
+  }
+  if (p.rt == 4)
     return p.gated ? launch_mtile_t<4, DT, true, true>(a, p.ks, s) : launch_mtile_t<4, DT, true, false>(a, p.ks, s);
   return p.rt == 8 && !p.exact && !p.gated ? launch_mtile_t<8, DT, false, false>(a, p.ks, s)
                                            : hipErrorInvalidValue;
