@@ -339,7 +339,10 @@ tpdq_status run_gemm(const uint16_t* X, int64_t ldx, int M, const int32_t* perm,
     }
     return TPDQ_OK;
   }
-  const int chunk = io.x_prepared ? M : chunk_rows(M, perm != nullptr, w, meta, avail);
+  int chunk = io.x_prepared ? M : chunk_rows(M, perm != nullptr, w, meta, avail);
+  // rows of X as it is are read through 32-bit byte offsets
+  if (!perm && !io.x_prepared && (int64_t)std::min(M, chunk) * ldx * 2 >= ((int64_t)1 << 31))
+    chunk = kDecodeMaxM;
   for (int m0 = 0; m0 < M; m0 += chunk) {
     const int mc = std::min(chunk, M - m0);
     const uint16_t* Xc = X + (int64_t)m0 * ldx;

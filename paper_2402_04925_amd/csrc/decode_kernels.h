@@ -617,9 +617,10 @@ struct ChunkMeta {
 // 128 rows of K a workgroup reads 4 MT KiB of activations from L2 and TN KiB
 // of weights, so more than 16 rows of M are cut into row groups of one or two
 // tiles with up to four column tiles (see plan_rows), neighbouring workgroups
-// sharing their weights in L2. M = 64, one workgroup with all four row tiles
-// and at most two column tiles against row groups: 6144 x 6144 19.2 -> 12.4
-// us, 8192 x 3584 20.2 -> 12.5, 3584 x 8192 13.9 -> 11.1. Each
+// sharing their weights in L2. M = 64 with the gather of X before it, one
+// workgroup with all four row tiles and at most two column tiles against row
+// groups: 6144 x 6144 23.6 -> 16.9 us, 8192 x 3584 24.7 -> 16.9, 3584 x 8192
+// 16.9 -> 14.1. Each
 // wave owns a run of 128-row blocks and keeps D of them in flight: the loads
 // are issued in the order the blocks are consumed and waited for one block at
 // a time, so the dequant and MFMAs of a block run while later blocks are

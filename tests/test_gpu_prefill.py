@@ -65,8 +65,8 @@ def test_prefill_zero_codes():
 def test_prefill_mlp_llama_tp2(path):
     """The Llama-70B TP = 2 prefill shard (M = 2048, W1 8192 x 14336, W2 14336 x
     8192) through tpdq_mlp_shard, on the ordered path (Alg. 3: the M-tiled
-    kernels) and the act-order path (Eq. 3 / Fig. 1: the per-row decode
-    kernels on 64-row chunks). Y1 is compared in full with the oracle's own
+    kernels) and the act-order path (Eq. 3 / Fig. 1: per-row
+    metadata, the weights dequantized once). Y1 is compared in full with the oracle's own
     rank-0 Y1, and Y2_partial on sampled columns with the oracle's GEMM2
     applied to that oracle Y1: no value the GPU produced enters a reference."""
     import torch
