@@ -470,7 +470,11 @@ hipError_t launch_permute_qweight(const uint32_t* src, int64_t ld_src, int K, in
   // repacking (no row permutation: already coalesced) word by word, as what
   // is not on 16 bytes (the caller's P and outputs may be on any word)
   const uintptr_t at = (uintptr_t)src | (uintptr_t)Prow | (uintptr_t)dst;
-  if (Prow && at % 16 == 0 && ld_src % 4 == 0 && K % 8 == 0 && N % 8 == 0) {
+  // ... and as small layers, whose gathers hit the caches and whose reorder the
+  // host's launches bound (pairs of K x N and N x K, word by word / through
+  // LDS: 1024 x 1024 93 / 119 us, 4096 x 2048 114-120 / 123, 4096 x 4096 171 / 117)
+  const bool large = (int64_t)K * N >= (int64_t)12 << 20;
+  if (Prow && large && at % 16 == 0 && ld_src % 4 == 0 && K % 8 == 0 && N % 8 == 0) {
     bool done = false;
     const hipError_t e =
         dst_layout == TPDQ_LAYOUT_TILED

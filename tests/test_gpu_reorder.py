@@ -159,11 +159,12 @@ def test_reorder_full_size(name):
 
 
 @pytest.mark.parametrize("K1,N1,N2,G", [
-    (20480, 40, 24, 128),     # the most rows a 16-column tile in LDS takes, ragged N
-    (20488, 40, 24, 8),       # past it: word by word
-    (136, 10248, 24, 64),     # W2: 8-column tiles (K2 > 10240), a partial last group, N2 % 16 == 8
-    (72, 40960, 8, 128),      # the widest row and the most rows the LDS passes take
-    (72, 40968, 8, 128),      # past both
+    (20480, 616, 24, 128),    # the most rows a 16-column tile in LDS takes, ragged N
+    (20488, 616, 24, 8),      # past it: word by word
+    (136, 10248, 1240, 64),   # W2: 8-column tiles (K2 > 10240), a partial last group, N2 % 16 == 8
+    (320, 40960, 312, 128),   # the widest row and the most rows the LDS passes take
+    (320, 40968, 312, 128),   # past both
+    (4096, 3072, 3064, 128),  # the smallest layers they take (12M codes), and one just smaller
 ])
 @pytest.mark.parametrize("layout", ["gptq", "tiled"])
 def test_reorder_lds_limits(K1, N1, N2, G, layout):
