@@ -134,9 +134,13 @@ bool rows_copy(int M, const tpdq_w4* w, size_t avail) {
          avail >= prepared_bytes(std::min(M, kRowsMaxM), w->K);
 }
 
-// Rows of one launch of the decode kernels.
-int chunk_rows(int M, bool perm, const tpdq_w4* w, int meta, size_t avail) {
-  return M > kDecodeMaxM && rows_route(M, perm, w, meta, avail) ? kRowsMaxM : kDecodeMaxM;
+// Rows of one launch of the decode kernels (the last launch of a call may have
+// fewer).
+int chunk_rows(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, size_t avail) {
+  if (M <= kDecodeMaxM || !rows_route(M, perm, w, meta, avail)) return kDecodeMaxM;
+  // rows of X as it is are read through 32-bit byte offsets
+  if (!perm && (int64_t)std::min(M, kRowsMaxM) * ldx * 2 >= ((int64_t)1 << 31)) return kDecodeMaxM;
+  return kRowsMaxM;
 }
 
 // The M-tiled kernel's plan when it covers the call. With a perm its row
@@ -222,14 +226,15 @@ size_t decode_part_bytes(const DecodePlan& p, int mc, int N) {
   return p.wide && p.ks > 1 ? align_up((size_t)p.ks * mc * N * 4) : 0;
 }
 
-// Row-major X with more than 32 rows, or more than 16 and K >= N, on tiled
-// weights of 16M to 64M elements: the header asks such a call for a workspace
-// of this size (split-K partials; the copy of X that it holds now is smaller).
+// Row-major X on large tiled weights (with more than 32 rows, or more than 16
+// and K >= N, from 16M elements on; with any more than 2 rows from 64M on): the
+// header asks such a call for a workspace of this size, split-K partials of one
+// launch of the wide kernel. Most of these calls run kernels that use less.
 size_t rowmajor_need(int M, const tpdq_w4* w, int meta) {
   const int mc = std::min(M, kDecodeMaxM);
   const int64_t kn = (int64_t)w->K * w->N;
   if (meta != kMetaGroup || !step_groups(w->group_size) || w->layout != TPDQ_LAYOUT_TILED ||
-      kn < ((int64_t)16 << 20) || kn >= kWideMinWeights || !(mc > 32 || (mc > 16 && w->K >= w->N)))
+      kn < ((int64_t)16 << 20) || !(mc > 32 || (mc > 16 && w->K >= w->N) || (mc > 2 && kn >= kWideMinWeights)))
     return 0;
   const int wgs = ((w->N + kTileN - 1) / kTileN + kWideWaves - 1) / kWideWaves;
   const int nblk = (w->K + 127) / 128;
@@ -239,7 +244,10 @@ size_t rowmajor_need(int M, const tpdq_w4* w, int meta) {
 
 // Bytes the call (X with leading dimension ldx, optional perm) uses. Decode:
 // [prepared operand][wide kernel's partials], the partials after the
-// prepared-operand region whenever either is used.
+// prepared-operand region of the largest launch whenever either is used. The
+// last launch of a call may have fewer rows and other kernels than the rest
+// (rows past 64 rows' multiple may take the wide kernel where 64 do not), so
+// every launch counts.
 size_t gemm_ws_need(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, int dt, bool gated,
                     size_t avail) {
   MtilePlan p;
@@ -249,14 +257,20 @@ size_t gemm_ws_need(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, i
   size_t gather = 0;
   if (dense_for(M, ldx, perm, w, meta, gated, avail, &gather, &ep))
     return gather + ep.w_bytes + ep.part_bytes;
-  DecodePlan dp;
-  bool prepared = false;
-  const int mc = std::min(M, chunk_rows(M, perm, w, meta, avail));  // the largest launch
-  const size_t legacy = !perm && !gated ? rowmajor_need(M, w, meta) : 0;
-  if (!decode_plan_for(mc, perm, w, meta, dt, &dp, &prepared, gated, nullptr, avail))
-    return perm ? decode_gather_bytes(M, w->K) : legacy;
-  const size_t part = decode_part_bytes(dp, mc, w->N);
-  return std::max(legacy, (prepared || part ? prepared_bytes(mc, w->K) : 0) + part);
+  const int chunk = std::min(M, chunk_rows(M, ldx, perm, w, meta, avail));
+  size_t need = !perm && !gated ? rowmajor_need(M, w, meta) : 0;
+  for (int mc : {chunk, M % chunk}) {
+    if (mc == 0) continue;
+    DecodePlan dp;
+    bool prepared = false;
+    if (!decode_plan_for(mc, perm, w, meta, dt, &dp, &prepared, gated, nullptr, avail)) {
+      if (perm) need = std::max(need, decode_gather_bytes(M, w->K));
+      continue;
+    }
+    const size_t part = decode_part_bytes(dp, mc, w->N);
+    need = std::max(need, (prepared || part ? prepared_bytes(chunk, w->K) : 0) + part);
+  }
+  return need;
 }
 
 int meta_mode(tpdq_path path) {
@@ -331,7 +345,8 @@ tpdq_status run_gemm(const uint16_t* X, int64_t ldx, int M, const int32_t* perm,
     a.ldy = ldy;
     hipError_t e;
     if (mtile) {
-      e = launch_mtile(a, mp, (float*)(ws + mtile_gather_bytes(M, w->K, perm != nullptr)), st);
+      e = launch_mtile(a, mp, mp.ks > 1 ? (float*)(ws + mtile_gather_bytes(M, w->K, perm != nullptr)) : nullptr,
+                       st);
       if (e != hipSuccess) return hip_fail(e, "M-tiled GEMM launch");
     } else {
       e = launch_dense16(a, ep, w->layout, ws + gather, st);
@@ -339,10 +354,7 @@ tpdq_status run_gemm(const uint16_t* X, int64_t ldx, int M, const int32_t* perm,
     }
     return TPDQ_OK;
   }
-  int chunk = io.x_prepared ? M : chunk_rows(M, perm != nullptr, w, meta, avail);
-  // rows of X as it is are read through 32-bit byte offsets
-  if (!perm && !io.x_prepared && (int64_t)std::min(M, chunk) * ldx * 2 >= ((int64_t)1 << 31))
-    chunk = kDecodeMaxM;
+  const int chunk = io.x_prepared ? M : std::min(M, chunk_rows(M, ldx, perm != nullptr, w, meta, avail));
   for (int m0 = 0; m0 < M; m0 += chunk) {
     const int mc = std::min(chunk, M - m0);
     const uint16_t* Xc = X + (int64_t)m0 * ldx;
@@ -400,8 +412,10 @@ tpdq_status run_gemm(const uint16_t* X, int64_t ldx, int M, const int32_t* perm,
       a.sc_up = (const uint16_t*)io.up->scales;
       a.qz_up = (const uint32_t*)io.up->qzeros;
     }
-    float* part = (float*)(ws + prepared_bytes(std::min(M, chunk), w->K));
-    hipError_t e = launch_decode(a, plan, part, st);
+    const size_t part_at = prepared_bytes(chunk, w->K), part_bytes = decode_part_bytes(plan, mc, w->N);
+    if (part_bytes && avail < part_at + part_bytes)  // what gemm_ws_need counts: never
+      return fail(TPDQ_ERR_WORKSPACE, "decode GEMM needs %zu workspace bytes, got %zu", part_at + part_bytes, avail);
+    hipError_t e = launch_decode(a, plan, part_bytes ? (float*)(ws + part_at) : nullptr, st);
     if (e != hipSuccess) return hip_fail(e, "decode GEMM launch");
   }
   return TPDQ_OK;
@@ -424,7 +438,8 @@ bool mlp_prepared_y1(int M, int64_t ldx, bool perm, const tpdq_w4* w1, const tpd
       mtile_for(M, w1->N, false, w2, meta, dt, false, avail, &mp))
     return false;
   if (M > kDecodeMaxM) {  // the row groups, X' and Y1' both in the workspace
-    return chunk_rows(M, perm, w1, meta, avail) >= M && chunk_rows(M, false, w2, meta, avail) >= M &&
+    return chunk_rows(M, ldx, perm, w1, meta, avail) >= M &&
+           chunk_rows(M, w1->N, false, w2, meta, avail) >= M &&
            prepared_bytes(M, w1->K) + prepared_bytes(M, w1->N) <= avail;
   }
   DecodePlan p1, p2;

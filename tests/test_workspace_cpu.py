@@ -1,0 +1,76 @@
+"""What a call does with its workspace, from its recorded launches (no GPU):
+every kernel stays inside the workspace and the outputs, and reads from the
+workspace only what an earlier launch of the call left there."""
+import os
+import random
+
+import pytest
+
+from paper_2402_04925_amd import _abi
+from tests import launches
+
+if not os.path.exists(_abi.LIB_PATH):
+    from paper_2402_04925_amd import build
+    build.build()
+
+
+@pytest.fixture(scope="module")
+def record(tmp_path_factory):
+    d = str(tmp_path_factory.mktemp("recorder"))
+    return lambda calls: launches.record(calls, d)
+
+
+def _log_uniform(rng, lo, hi, step):
+    return max(step, round(lo * (hi / lo) ** rng.random() / step) * step)
+
+
+def _random_call(rng):
+    op = rng.choice(["gemm", "gemm", "mlp", "gated", "noalloc"])
+    step = rng.choice([8, 16, 128, 512])
+    top = rng.choice([2000, 9000, 40000])
+    K, N, N2 = (_log_uniform(rng, 8, top, step) for _ in range(3))
+    G, path = rng.choice([8, 24, 32, 64, 128, 128, 256, 0]), rng.choice(["ordered", "ordered", "actorder", "global"])
+    c = dict(op=op, M=_log_uniform(rng, 1, rng.choice([70, 300, 3000]), 1), K=K, N=N, N2=0 if op == "gemm" else N2,
+             G=G, path=path, layout=rng.choice(["tiled", "gptq"]), dtype=rng.choice(["fp16", "bf16"]),
+             perm=rng.random() < 0.4, gidx=path != "ordered" or G == 0 or rng.random() < 0.5)
+    if rng.random() < 0.25:  # rows far apart: past 32-bit offsets from about 1000 rows on
+        c["ldx"] = rng.choice([1 << 20, 1 << 21, 1 << 22])
+    if G == 0:
+        c["ng1"], c["ng2"] = rng.choice([5, 400]), rng.choice([5, 400])
+    elif path != "ordered" and rng.random() < 0.5:  # a row shard of eight
+        c["ng2"] = -(-N * 8 // G)
+    return c
+
+
+@pytest.mark.parametrize("ws", ["doc", 0, 4096, 1 << 20, 16 << 20, None])
+def test_random_calls_stay_inside(record, ws):
+    rng = random.Random(str(ws))
+    calls = [dict(_random_call(rng), ws=ws) for _ in range(400)]
+    done = 0
+    for c, r in zip(calls, record(calls)):
+        assert launches.outside(r) == [], c
+        assert r["status"] in (_abi.OK, _abi.ERR_WORKSPACE, _abi.ERR_UNSUPPORTED), c
+        assert ws != "doc" or c["op"] == "noalloc" or r["status"] != _abi.ERR_WORKSPACE, c
+        done += r["status"] == _abi.OK
+    assert done > 80
+
+
+# Row-major X that the M-tiled kernel refuses (2 GiB or more) on large tiled
+# weights is cut into launches of 64 rows; the last one, of 1 to 32 rows, takes
+# the wide kernel, whose split-K partials the others do not use.
+@pytest.mark.parametrize("op", ["mlp", "gated"])
+@pytest.mark.parametrize("M", [131088, 131100])
+def test_last_launch_of_many(record, op, M):
+    (r,) = record([dict(op=op, M=M, K=8192, N=28672, N2=8192)])
+    assert r["status"] == _abi.OK
+    assert launches.outside(r) == []
+    assert "k_wide" in r["launches"][-2]["kernel"] and "reduce" in r["launches"][-1]["kernel"]
+
+
+@pytest.mark.parametrize("M,ldx", [(1040, 1 << 20), (1024, 1 << 20), (131082, 8192), (131072, 8192)])
+@pytest.mark.parametrize("ws", [None, 4096])
+def test_large_row_major_calls_need_their_workspace(record, M, ldx, ws):
+    c = dict(op="gemm", M=M, K=8192, N=8192, ldx=ldx)
+    short, full = record([dict(c, ws=ws), c])
+    assert short["status"] == _abi.ERR_WORKSPACE and short["launches"] == []
+    assert full["status"] == _abi.OK and launches.outside(full) == []
