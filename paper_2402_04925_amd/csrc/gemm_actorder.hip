@@ -332,19 +332,23 @@ bool plan_dense16(int M, int64_t ldx, const tpdq_w4* w, bool gated, size_t budge
   }
   q.w_bytes = align_up((size_t)((q.ncols + 15) / 16 * 16) * (size_t)cb);
   const int nblk = (K + 127) / 128;
-  double best = 1e30;
-  for (int rt : {8, 4})
-    for (int ks = 1; ks <= std::max(1, nblk / 4); ++ks) {
-      const size_t part = ks > 1 ? align_up((size_t)ks * M * q.ncols * (gated ? 8 : 4)) : 0;
-      if (part && (q.w_bytes + part > budget || part > kDenseChunkBytes / 2)) break;
-      const double cost = dense_cost(M, q.ncols, nblk, rt, ks, gated);
-      if (cost < 0.98 * best) {
-        best = cost;
-        q.rt = rt;
-        q.ks = ks;
-        q.part_bytes = part;
+  // as in plan_mtile: the choice without a limit, where the workspace holds it
+  for (size_t limit : {SIZE_MAX, budget}) {
+    double best = 1e30;
+    for (int rt : {8, 4})
+      for (int ks = 1; ks <= std::max(1, nblk / 4); ++ks) {
+        const size_t part = ks > 1 ? align_up((size_t)ks * M * q.ncols * (gated ? 8 : 4)) : 0;
+        if (part && (q.w_bytes + part > limit || part > kDenseChunkBytes / 2)) break;
+        const double cost = dense_cost(M, q.ncols, nblk, rt, ks, gated);
+        if (cost < 0.98 * best) {
+          best = cost;
+          q.rt = rt;
+          q.ks = ks;
+          q.part_bytes = part;
+        }
       }
-    }
+    if (q.w_bytes + q.part_bytes <= budget) break;
+  }
   if (q.w_bytes > budget) return false;
   *p = q;
   return true;

@@ -528,24 +528,30 @@ bool plan_mtile(int M, int64_t ldx, const tpdq_w4* w, int meta, int dt, bool gat
   // at M = 1000: 128 tiles of 128 x 512 on 256 CUs 84.7 us, 256 of 64 x 512
   // 67.8 us; 6144 x 6144 at M = 512: 133.6 us, 57.5 us with 64-row tiles and
   // K split 2
-  double best = 1e30;
-  for (int rt : {8, 4}) {
-    if (exact && rt == 8) continue;
-    for (int ks = 1; ks <= std::max(1, nblk / 4); ++ks) {
-      MtilePlan c = q;
-      c.rt = rt;
-      c.ks = ks;
-      c.exact = rt == 4;
-      if (ks > 1 && (!optional || mtile_part_bytes(c, M, N) > part_budget ||
-                     (int64_t)ks * M * N * (gated ? 8 : 4) >= lim))
-        break;
-      const double cost = mtile_cost(M, N, nblk, rt, ks, gated, dt);
-      if (cost < 0.98 * best) {
-        best = cost;
-        c.cost = cost;
-        *p = c;
+  // Chosen without a limit on the workspace first, so that every workspace that
+  // holds the choice gives the same one (a workspace that other calls have made
+  // larger must not change the order of a call's sums).
+  for (size_t budget : {SIZE_MAX, part_budget}) {
+    double best = 1e30;
+    for (int rt : {8, 4}) {
+      if (exact && rt == 8) continue;
+      for (int ks = 1; ks <= std::max(1, nblk / 4); ++ks) {
+        MtilePlan c = q;
+        c.rt = rt;
+        c.ks = ks;
+        c.exact = rt == 4;
+        if (ks > 1 && (!optional || mtile_part_bytes(c, M, N) > budget ||
+                       (int64_t)ks * M * N * (gated ? 8 : 4) >= lim))
+          break;
+        const double cost = mtile_cost(M, N, nblk, rt, ks, gated, dt);
+        if (cost < 0.98 * best) {
+          best = cost;
+          c.cost = cost;
+          *p = c;
+        }
       }
     }
+    if (mtile_part_bytes(*p, M, N) <= part_budget) break;
   }
   return true;
 }

@@ -74,3 +74,21 @@ def test_large_row_major_calls_need_their_workspace(record, M, ldx, ws):
     short, full = record([dict(c, ws=ws), c])
     assert short["status"] == _abi.ERR_WORKSPACE and short["launches"] == []
     assert full["status"] == _abi.OK and launches.outside(full) == []
+
+
+def test_route_does_not_depend_on_spare_workspace(record):
+    """Any workspace of the documented size or more takes the same kernels with
+    the same splits, so that results do not change with what other calls have
+    made a shared workspace grow to."""
+    rng = random.Random(7)
+    calls = [dict(op="mlp", M=257, K=9224, N=2752, N2=40, G=24, path="actorder", layout="gptq", dtype="bf16"),
+             dict(op="gemm", M=700, K=9224, N=2752, path="actorder", layout="gptq")]
+    calls += [dict(c, M=rng.randint(1, 1500)) for c in (_random_call(rng) for _ in range(1500)) if c["op"] != "noalloc"]
+    exact, spare = record(calls), record([dict(c, ws="2doc") for c in calls])
+    much = record([dict(c, ws=4 << 30) for c in calls])
+    for c, a, b, d in zip(calls, exact, spare, much):
+        assert launches.route(a) == launches.route(b) == launches.route(d), c
+    # ... and so does the library's own scratch, where the documented size fits
+    mlp = [(c, r) for c, r in zip(calls, exact) if c["op"] == "mlp" and r["doc"] <= launches.SCRATCH_BYTES]
+    for (c, r), n in zip(mlp, record([dict(c, op="noalloc") for c, _ in mlp])):
+        assert launches.route(r) == launches.route(n), c
