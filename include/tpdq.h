@@ -291,8 +291,12 @@ tpdq_status tpdq_gated_mlp_shard(const void* X, int64_t ldx, int32_t M, const in
 /* Workspace bytes for op 0 (tpdq_reorder: a = w1, b = w2 or NULL),
  * 1 (tpdq_w4a16_gemm: a = w), 2 (tpdq_mlp_shard: a = w1, b = w2) or
  * 3 (tpdq_gated_mlp_shard: a = w_gate, b = w_down) at batch M: what the
- * fastest routes take. A call accepts less where a slower route of it does
- * with less. Returns 0 when the arguments are invalid. */
+ * fastest routes take, on the costliest path that the layers allow. A call
+ * accepts less where a slower route of it does with less. An ordered call with
+ * group_size > 0 reads no g_idx: leave it NULL in the layers of such a call (here
+ * and in the call), or the size covers the act-order path too, whose
+ * dequantized weights take up to 128 MiB more above 64 rows. Returns 0 when the
+ * arguments are invalid. */
 size_t tpdq_workspace_bytes(int op, int32_t M, const tpdq_w4* a, const tpdq_w4* b);
 
 /* Static description of a status code. */

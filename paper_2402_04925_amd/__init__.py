@@ -130,7 +130,10 @@ class QuantWeight:
         ng = scales.shape[0] if num_groups is None else num_groups
         return cls(qweight, scales, qzeros, g_idx, K, N, G, ng, LAYOUT_GPTQ, zero_offset)
 
-    def c_struct(self) -> _abi.W4:
+    def c_struct(self, path: Optional[int] = None) -> _abi.W4:
+        """The C struct. With PATH_ORDERED and G > 0 it leaves out g_idx, which
+        such a call never reads: the workspace of a layer with one also covers
+        the act-order routes."""
         torch = _torch()
         q, s, z, g = self.qweight, self.scales, self.qzeros, self.g_idx
         # every condition of the loops below in one expression (a call makes one
@@ -141,6 +144,8 @@ class QuantWeight:
                 and q.stride(1) == 1 and s.stride(1) == 1 and z.stride(1) == 1
                 and (g is None or (g.dtype is i32 and g.device == dev and g.is_contiguous()))):
             self._check_tensors()
+        if path == PATH_ORDERED and self.G > 0:
+            g = None
         # positional, in the field order of the C struct
         return _abi.W4(q.data_ptr(), q.stride(0), s.data_ptr(), s.stride(0), z.data_ptr(), z.stride(0),
                        None if g is None else g.data_ptr(), self.K, self.N, self.G, self.num_groups,
@@ -308,7 +313,7 @@ def w4a16_gemm(X, w: QuantWeight, path: int, x_perm=None, out=None,
     _check_out("out", out, M, w.N, X.dtype)
     if out is None:
         out = torch.empty(M, w.N, dtype=X.dtype, device=X.device)
-    cw = w.c_struct()
+    cw = w.c_struct(path)
     lib = _abi.lib()
     nbytes = lib.tpdq_workspace_bytes(OP_GEMM, M, ctypes.byref(cw), None)
     buf = _workspace(X.device, nbytes, workspace)
@@ -334,7 +339,7 @@ def mlp_shard(X, w1: QuantWeight, w2: QuantWeight, path: int, P1=None, y1=None, 
         y1 = torch.empty(M, w1.N, dtype=X.dtype, device=X.device)
     if y2 is None:
         y2 = torch.empty(M, w2.N, dtype=X.dtype, device=X.device)
-    c1, c2 = w1.c_struct(), w2.c_struct()
+    c1, c2 = w1.c_struct(path), w2.c_struct(path)
     lib = _abi.lib()
     nbytes = lib.tpdq_workspace_bytes(OP_MLP, M, ctypes.byref(c1), ctypes.byref(c2))
     buf = _workspace(X.device, nbytes, workspace)
@@ -386,7 +391,7 @@ def gated_mlp_shard(X, w_gate: QuantWeight, w_up: QuantWeight, w_down: QuantWeig
         y1 = torch.empty(M, w_gate.N, dtype=X.dtype, device=X.device)
     if y2 is None:
         y2 = torch.empty(M, w_down.N, dtype=X.dtype, device=X.device)
-    cg, cu, cd = w_gate.c_struct(), w_up.c_struct(), w_down.c_struct()
+    cg, cu, cd = w_gate.c_struct(path), w_up.c_struct(path), w_down.c_struct(path)
     lib = _abi.lib()
     nbytes = lib.tpdq_workspace_bytes(OP_GATED_MLP, M, ctypes.byref(cg), ctypes.byref(cd))
     buf = _workspace(X.device, nbytes, workspace)

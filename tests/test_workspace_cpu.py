@@ -92,3 +92,49 @@ def test_route_does_not_depend_on_spare_workspace(record):
     mlp = [(c, r) for c, r in zip(calls, exact) if c["op"] == "mlp" and r["doc"] <= launches.SCRATCH_BYTES]
     for (c, r), n in zip(mlp, record([dict(c, op="noalloc") for c, _ in mlp])):
         assert launches.route(r) == launches.route(n), c
+
+
+class _Library:
+    """The library up to its launches: keeps the workspace bytes of each call."""
+
+    def __init__(self, lib):
+        self._lib, self.got = lib, []
+
+    def __getattr__(self, name):
+        if name in ("tpdq_w4a16_gemm", "tpdq_mlp_shard", "tpdq_gated_mlp_shard"):
+            return lambda *args: self.got.append(args[-2]) or _abi.OK
+        return getattr(self._lib, name)
+
+
+def test_ordered_calls_ask_for_no_act_order_workspace(monkeypatch):
+    """A layer of reorder() carries its sorted g_idx; an ordered call of it asks
+    for what the same layer without one does, and an act-order call for more."""
+    import torch
+    import paper_2402_04925_amd as tpdq
+    lib = _Library(_abi.lib())
+    monkeypatch.setattr(_abi, "lib", lambda: lib)
+    monkeypatch.setattr(tpdq, "_check_args", lambda *a, **k: None)
+    monkeypatch.setattr(tpdq, "_stream_handle", lambda d: 0)
+
+    def layer(K, N, gidx):
+        G = 128
+        return tpdq.QuantWeight(
+            torch.empty(N // 16, tpdq.tiled_ld(K), dtype=torch.int32), torch.empty(K // G, N, dtype=torch.float16),
+            torch.empty(K // G, N // 8, dtype=torch.int32),
+            torch.zeros(K, dtype=torch.int32) if gidx else None, K, N, G, K // G, tpdq.LAYOUT_TILED)
+
+    M, K, N = 300, 8192, 3584
+    X, P = torch.empty(M, K, dtype=torch.float16), torch.zeros(K, dtype=torch.int32)
+
+    def sizes(gidx, path):
+        a, b = layer(K, N, gidx), layer(N, K, gidx)
+        perm = P if path == tpdq.PATH_ORDERED else None
+        lib.got.clear()
+        tpdq.w4a16_gemm(X, a, path, x_perm=perm, workspace=tpdq.Workspace())
+        tpdq.mlp_shard(X, a, b, path, P1=perm, workspace=tpdq.Workspace())
+        tpdq.gated_mlp_shard(X, a, a, b, path, P1=perm, workspace=tpdq.Workspace())
+        return list(lib.got)
+
+    ordered = sizes(True, tpdq.PATH_ORDERED)
+    assert len(ordered) == 3 and ordered == sizes(False, tpdq.PATH_ORDERED)
+    assert all(a > o for a, o in zip(sizes(True, tpdq.PATH_ACTORDER), ordered))
