@@ -72,6 +72,64 @@ __device__ __forceinline__ u4_t dequant_scaled_bf16(const UnpackConsts<kBF16>& k
   return r;
 }
 
+// bf16, EXACT: an infinite x, or a finite one past about 2e36, makes both of a
+// group's sums infinite and their difference NaN. The elements that came out
+// not finite (bits of `again`, see k_prefill) are summed again here with every
+// weight s (q - z) rounded to bf16, as the 128-row tiles take them, so that each
+// product has its own sign and size; what is finite keeps its bits. One wave for
+// itself, straight from global memory, a tile at a time: for rare inputs only,
+// so nothing of it may cost the kernel registers.
+template <int SPG, int RT, bool GATED>
+__device__ __forceinline__ void round_not_finite(const GemmArgs& a, uint64_t again, int row0, int cw, int kb0,
+                                                 int kb1, float* part) {
+  constexpr int COLT = GATED ? 2 : kPWT;
+  // counted anew: threadIdx held through the kernel's loop is a register it has not
+  const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  const int j = lane & 15, kq = lane >> 4;
+  const size_t plane = (size_t)a.M * a.N;
+  const UnpackConsts<kBF16> kc;
+#pragma unroll 1
+  for (int t = 0; t < RT * COLT; ++t) {
+    const int r = t / COLT, i = t % COLT;
+    uint32_t bits = (uint32_t)(again >> ((r * kPWT + i) * 4)) & 15u;
+    if (GATED) bits |= (uint32_t)(again >> ((r * kPWT + i + 2) * 4)) & 15u;
+    if (!__any(bits != 0)) continue;
+    const int c = cw + 16 * i + j;
+    const bool cok = c < a.N;
+    f4_t v[2] = {f4_t{0.f, 0.f, 0.f, 0.f}, f4_t{0.f, 0.f, 0.f, 0.f}};
+    const int m = row0 + 16 * r + j;  // the lane's row of the A operand
+#pragma unroll 1
+    for (int s = 4 * kb0; s < 4 * kb1; ++s) {
+      const int k0 = 32 * s + 8 * kq;
+      u4_t x = {0u, 0u, 0u, 0u};
+      if (m < a.M && k0 < a.K) x = *(const u4_t*)(a.X + (int64_t)m * a.ldx + k0);
+      const int64_t g = s / SPG;
+#pragma unroll
+      for (int p = 0; p < (GATED ? 2 : 1); ++p) {
+        uint32_t w = 0u, zc = 0u;
+        float sf = 0.f;
+        if (cok && 32 * s < a.K) {
+          w = (p ? a.qw_up : a.qw)[(int64_t)(c >> 4) * a.ldq + 256 * (s >> 2) + 4 * lane + (s & 3)];
+          sf = bits_to_float<kBF16>((p ? a.sc_up : a.sc)[g * a.lds + c]);
+          zc = (((p ? a.qz_up : a.qz)[g * a.ldz + (c >> 3)] >> (4 * (c & 7))) & 0xFu) + (uint32_t)a.zoff;
+        }
+        v[p] = mfma_k32<kBF16>(x, dequant_scaled_bf16(kc, w, sf, (128.f + (float)zc) * sf), v[p]);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int row = row0 + 16 * r + 4 * kq + e;
+      if (!((bits >> e) & 1u) || row >= a.M || !cok) continue;
+      if (a.ks > 1) {
+        part[(int64_t)row * a.N + c] = v[0][e];
+        if constexpr (GATED) part[plane + (int64_t)row * a.N + c] = v[1][e];
+      } else {
+        a.Y[(int64_t)row * a.ldy + c] = float_to_bits<kBF16>(GATED ? silu_mul(v[0][e], v[1][e]) : v[0][e]);
+      }
+    }
+  }
+}
+
 // RT row tiles (16 RT rows of Y per workgroup), NW waves (64 columns each),
 // ST stages (2 or 3) of LDS. With a.ks > 1 the workgroup covers one of ks
 // contiguous ranges of 128-row blocks of K and writes its fp32 partial tile
@@ -374,6 +432,17 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
         }
       }
     }
+  if constexpr (EXACT && DT == kBF16) {
+    uint64_t again = 0;  // element e of tile i, row tile r: bit (r kPWT + i) 4 + e
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int i = 0; i < kPWT; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (!__builtin_isfinite(acc[r][i][e])) again |= 1ull << ((r * kPWT + i) * 4 + e);
+    if (__any(again != 0)) round_not_finite<SPG, RT, GATED>(a, again, row0, cw, kb0, kb1, part);
+  }
 }
 
 // Y[m][n] = round(sum over s of part[s][m][n]) to the element type, the splits added in order s =

@@ -139,3 +139,60 @@ def test_small_workspace_keeps_its_route(M):
     torch.cuda.synchronize()
     assert o.rel_err(np_of(y), _product(X, l)) <= TOL["fp16"]
     assert o.rel_err(np_of(yp), _product(X[:, np_of(P)], l)) <= TOL["fp16"]
+
+
+# 64-row tiles at prefill sizes, without and with a K split, whole and ragged,
+# every group size; 64-row tiles of large weights below them
+NOT_FINITE = [(300, 4096, 1032, 128), (256, 1000, 264, 32), (700, 8192, 520, 256), (257, 1064, 1160, 64),
+              (300, 512, 8192, 128), (64, 8192, 8200, 128)]
+
+
+@pytest.mark.parametrize("M,K,N,G", NOT_FINITE)
+def test_not_finite_activations(M, K, N, G):
+    """bf16: an infinite x gives each column +-Inf (NaN where the weight is 0),
+    a very large one its finite product, and the other rows are as without."""
+    import torch
+    import paper_2402_04925_amd as tpdq
+    dev = torch_dev()
+    log(f"not finite M={M} K={K} N={N} G={G}")
+    (l,) = _layers(K, N, G, "bf16", 1)
+    w = tpdq.pack_tiled(layer_to_dev(l, dev, with_gidx=False))
+    X = _x(M, K, "bf16")
+    clean = tpdq.w4a16_gemm(to_dev(X, dev, True), w, tpdq.PATH_ORDERED)
+    X[3, 5], X[M - 1, K - 1] = np.inf, -np.inf
+    X[17, 33], X[17, K - 2] = 2.0**126, -(2.0**125)
+    bad = [3, 17, M - 1]
+    y = tpdq.w4a16_gemm(to_dev(X, dev, True), w, tpdq.PATH_ORDERED)
+    torch.cuda.synchronize()
+    rest = [m for m in range(M) if m not in bad]
+    assert torch.equal(y[rest], clean[rest])
+    W = o.dequant(l.qweight, l.scales, l.qzeros, l.g_idx)
+    with np.errstate(invalid="ignore"):
+        ref = X[bad].astype(np.float64) @ W
+    got = np_of(y[bad])
+    for i in (0, 2):
+        np.testing.assert_array_equal(got[i], ref[i])
+    # weights rounded to bf16 (2^-9 each) and the result once
+    assert np.isfinite(got[1]).all() and o.rel_err(got[1], ref[1]) <= 2.0**-7
+
+
+def test_not_finite_activations_gated():
+    """The gate overflows its sums, the up projection scales it back."""
+    import torch
+    import paper_2402_04925_amd as tpdq
+    dev = torch_dev()
+    M, K, N = 130, 1064, 520
+    gate, up = _layers(K, N, 128, "bf16", 2)
+    up.scales = (up.scales * 2.0**-120).astype(up.scales.dtype)
+    down = _layers(N, 64, 8, "bf16", 1)[0]
+    X = _x(M, K, "bf16")
+    X[7, 9] = 2.0**124
+    ws = [tpdq.pack_tiled(layer_to_dev(l, dev, with_gidx=False)) for l in (gate, up, down)]
+    y1, _ = tpdq.gated_mlp_shard(to_dev(X, dev, True), *ws, tpdq.PATH_ORDERED,
+                                 P1=to_dev(np.arange(K, dtype=np.int32), dev))
+    torch.cuda.synchronize()
+    with np.errstate(over="ignore"):
+        ref = o.silu(_product(X[7:8], gate)) * _product(X[7:8], up)
+    got = np_of(y1[7:8])
+    # both products of bf16 weights (2^-9 each), one rounding
+    assert np.isfinite(got).all() and o.rel_err(got, ref) <= 2.0**-6
