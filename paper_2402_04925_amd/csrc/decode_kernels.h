@@ -66,11 +66,11 @@ __device__ __forceinline__ void load_groups(const GemmArgs& a, bool ok, int wr, 
 // ---------------------------------------------------------------------------
 
 // Metadata of the 16-column tile (kMetaRowLds): one entry of W words per
-// (group, column), the scale's bits | (0x6400 | z) << 16 (the zero as fp16
+// (group, column), the scale's bits | z << 16 (fp16: 0x6400 | z, the zero as
 // 1024 + z) in word COMP (0; the gated kernel's up projection in word 1 of 2).
 // Entries of 4 (8) bytes: a wave's 64 lanes read four groups' 16 neighbouring
 // words, at 16 bytes apart they met on a quarter of the banks.
-template <int NT, int R, int W, int COMP = 0>
+template <int NT, int R, int DT, int W, int COMP = 0>
 struct MetaStage {
   uint32_t s[R], z[R];
   // Entry idx = 16 g + c: group g, column n0 + c. The loads are branch-free:
@@ -92,7 +92,7 @@ struct MetaStage {
   __device__ __forceinline__ static void put(uint32_t* meta, int idx, int n, uint32_t sbits,
                                              uint32_t zw, int zoff) {
     const uint32_t zc = ((zw >> (4 * (n & 7))) & 0xFu) + (uint32_t)zoff;
-    meta[idx * W + COMP] = sbits | ((0x6400u | zc) << 16);
+    meta[idx * W + COMP] = sbits | ((DT == kBF16 ? zc : 0x6400u | zc) << 16);
   }
   // Entries past the last group go to the spare entry meta[items], so every
   // value loaded in load() is consumed on every path (a value used only
@@ -1074,11 +1074,14 @@ __global__ __launch_bounds__(NW * 64) void k_wide(GemmArgs a) {
 // ---------------------------------------------------------------------------
 // Row-metadata kernel: each of the 8 rows of a word looks its group up
 // (g_idx, or floor(k / G) when g_idx is NULL) and is dequantized on its own.
-// One 128-row block of weights (and, kMetaRowGlobal, of g_idx) is prefetched
-// ahead. kMetaRowLds is bound by its VALU and LDS work per word, 8 lookups and
-// 8 dequantizations: the tile's metadata and every row's entry offset are in
-// LDS, so that a lookup is one address operation and one 4-byte read, and two
-// byte permutes make the zero and scale pairs of packed fp16 arithmetic.
+// One 128-row block of weights (and of g_idx, where the rows' offsets are not in
+// LDS) is prefetched ahead. kMetaRowLds is bound by its VALU and LDS work per
+// word, 8 lookups and 8 dequantizations: the tile's metadata and every row's
+// entry offset are in LDS, so that a lookup is one address operation and one
+// 4-byte read, and two byte permutes make the zero and scale pairs of packed
+// fp16 arithmetic. kMetaRowLdsIdx keeps the metadata there and reads the groups
+// from g_idx, a clamp and a shift more per row: 65536 x 288, G = 128 in fp16 at
+// M = 16, all metadata from global memory 496 us, here 89.
 // ---------------------------------------------------------------------------
 template <int MT, int NW, int META, int AM, int LAYOUT, int DT, bool GATED = false>
 __global__ __launch_bounds__(NW * 64) void k_rowmeta(GemmArgs a) {
@@ -1100,6 +1103,7 @@ __global__ __launch_bounds__(NW * 64) void k_rowmeta(GemmArgs a) {
   const int nblk = (a.K + 127) >> 7;
   const int b0 = (int)((int64_t)nblk * wave / NW);
   const int b1 = (int)((int64_t)nblk * (wave + 1) / NW);
+  constexpr bool ENTRIES = META == kMetaRowLds || META == kMetaRowLdsIdx;  // metadata in LDS
   constexpr int MW = GATED ? 2 : 1;  // words per metadata entry
   uint32_t* meta = (uint32_t*)smem;
   uint16_t* gl = (uint16_t*)(smem + a.lds_g_off);
@@ -1119,10 +1123,10 @@ __global__ __launch_bounds__(NW * 64) void k_rowmeta(GemmArgs a) {
   const uint32_t* qtile_u = au.qw + (int64_t)tile * a.ldq;
 
   constexpr int MR = 4096 / NT < 8 ? 4096 / NT : 8;
-  MetaStage<NT, MR, MW> ms;
-  MetaStage<NT, MR, MW, MW - 1> msu;
-  if constexpr (META == kMetaRowLds) ms.load(a, n0, a.meta_rows, tid);
-  if constexpr (META == kMetaRowLds && GATED) msu.load(au, n0, a.meta_rows, tid);
+  MetaStage<NT, MR, DT, MW> ms;
+  MetaStage<NT, MR, DT, MW, MW - 1> msu;
+  if constexpr (ENTRIES) ms.load(a, n0, a.meta_rows, tid);
+  if constexpr (ENTRIES && GATED) msu.load(au, n0, a.meta_rows, tid);
   XStage<NT, false, LAYOUT> xst;
   if constexpr (!AG) xst.load(a, tid);
 
@@ -1142,11 +1146,11 @@ __global__ __launch_bounds__(NW * 64) void k_rowmeta(GemmArgs a) {
   u4_t ab[4][MT];
   if constexpr (AG) load_a_block<MT, AM, LAYOUT>(a, j, kq, b0, b0 < b1, kw, ab);
 
-  if constexpr (META == kMetaRowLds) ms.store(a, meta, n0, a.meta_rows, tid);
-  if constexpr (META == kMetaRowLds && GATED) msu.store(au, meta, n0, a.meta_rows, tid);
+  if constexpr (ENTRIES) ms.store(a, meta, n0, a.meta_rows, tid);
+  if constexpr (ENTRIES && GATED) msu.store(au, meta, n0, a.meta_rows, tid);
   if constexpr (META == kMetaRowLds) stage_groups<NT, MW - 1>(a, gl, a.meta_rows, tid);
   if constexpr (!AG) xst.store(a, xs, nullptr, tid);
-  if constexpr (META == kMetaRowLds || !AG) __syncthreads();
+  if constexpr (ENTRIES || !AG) __syncthreads();
   AAddr aa[MT];
 #pragma unroll
   for (int t = 0; t < MT; ++t) aa[t].init(a.M, j, kq, t, zero_slot);
@@ -1188,13 +1192,15 @@ __global__ __launch_bounds__(NW * 64) void k_rowmeta(GemmArgs a) {
           av[t] = xs[aa[t].base + aa[t].stride * (4 * b + u)];
       }
       u4_t bv, bvu;
-      if constexpr (META == kMetaRowLds) {
+      if constexpr (ENTRIES) {
         // the eight rows' entry offsets, two to a word
-        const u4_t gp = *(const u4_t*)(gl + 128 * b + 32 * u + 8 * kq);
+        u4_t gp = {0u, 0u, 0u, 0u};
+        if constexpr (META == kMetaRowLds) gp = *(const u4_t*)(gl + 128 * b + 32 * u + 8 * kq);
         uint32_t e[8], eu[8];
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
-          const uint32_t o16 = (r & 1) ? gp[r >> 1] >> 16 : gp[r >> 1] & 0xFFFFu;
+          uint32_t o16 = (r & 1) ? gp[r >> 1] >> 16 : gp[r >> 1] & 0xFFFFu;
+          if constexpr (META == kMetaRowLdsIdx) o16 = min(r < 4 ? gb[u][0][r] : gb[u][1][r - 4], gmax) << 6;
           const uint32_t at = (o16 << (MW - 1)) + meta_at;
           if constexpr (GATED) {
             const uint64_t v = *(lds_u64_t)(uintptr_t)at;
@@ -1301,12 +1307,23 @@ DecodeKernel pick_ordered_spg(int spg, int am, int tn) {
   return nullptr;
 }
 
-template <int MT, int NW, int L, int META, int DT>
+template <int MT, int NW, int L, int META, int DT, bool GATED>
 DecodeKernel pick_row_am(int am) {
   switch (am) {
-    case kAGlobal: return k_rowmeta<MT, NW, META, kAGlobal, L, DT>;
-    case kAGlobalPrep: return k_rowmeta<MT, NW, META, kAGlobalPrep, L, DT>;
-    case kALds: return k_rowmeta<MT, NW, META, kALds, L, DT>;
+    case kAGlobal: return k_rowmeta<MT, NW, META, kAGlobal, L, DT, GATED>;
+    case kAGlobalPrep: return k_rowmeta<MT, NW, META, kAGlobalPrep, L, DT, GATED>;
+    case kALds:  // not where LDS has no room for the rows' offsets (plan_decode)
+      if constexpr (META != kMetaRowLdsIdx) return k_rowmeta<MT, NW, META, kALds, L, DT, GATED>;
+  }
+  return nullptr;
+}
+
+template <int MT, int NW, int L, int DT, bool GATED>
+DecodeKernel pick_row(const DecodePlan& p) {
+  if (p.meta == kMetaRowLds) return pick_row_am<MT, NW, L, kMetaRowLds, DT, GATED>(p.amode);
+  if constexpr (NW <= 8) {
+    return p.meta == kMetaRowLdsIdx ? pick_row_am<MT, NW, L, kMetaRowLdsIdx, DT, GATED>(p.amode)
+                                    : pick_row_am<MT, NW, L, kMetaRowGlobal, DT, GATED>(p.amode);
   }
   return nullptr;
 }
@@ -1314,10 +1331,7 @@ DecodeKernel pick_row_am(int am) {
 template <int MT, int NW, int L, int DT>
 DecodeKernel pick_mt_nw(const DecodePlan& p) {
   if (p.meta == kMetaGroup) return pick_ordered_spg<MT, NW, L, DT>(p.spg, p.amode, p.tn);
-  if constexpr (!(MT == 4 && NW > 4) && (NW <= 8 || MT == 1)) {
-    if (p.meta == kMetaRowLds) return pick_row_am<MT, NW, L, kMetaRowLds, DT>(p.amode);
-    if constexpr (NW <= 8) return pick_row_am<MT, NW, L, kMetaRowGlobal, DT>(p.amode);
-  }
+  if constexpr (!(MT == 4 && NW > 4) && (NW <= 8 || MT == 1)) return pick_row<MT, NW, L, DT, false>(p);
   return nullptr;
 }
 
@@ -1394,20 +1408,7 @@ DecodeKernel pick_gated_mt_nw(const DecodePlan& p) {
     }
     return nullptr;
   }
-  if constexpr (!(MT == 4 && NW > 4)) {
-    const bool lds = p.meta == kMetaRowLds;
-    switch (p.amode) {
-      case kAGlobal:
-        return lds ? k_rowmeta<MT, NW, kMetaRowLds, kAGlobal, L, DT, true>
-                   : k_rowmeta<MT, NW, kMetaRowGlobal, kAGlobal, L, DT, true>;
-      case kAGlobalPrep:
-        return lds ? k_rowmeta<MT, NW, kMetaRowLds, kAGlobalPrep, L, DT, true>
-                   : k_rowmeta<MT, NW, kMetaRowGlobal, kAGlobalPrep, L, DT, true>;
-      case kALds:
-        return lds ? k_rowmeta<MT, NW, kMetaRowLds, kALds, L, DT, true>
-                   : k_rowmeta<MT, NW, kMetaRowGlobal, kALds, L, DT, true>;
-    }
-  }
+  if constexpr (!(MT == 4 && NW > 4)) return pick_row<MT, NW, L, DT, true>(p);
   return nullptr;
 }
 

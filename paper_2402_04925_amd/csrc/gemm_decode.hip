@@ -150,11 +150,14 @@ bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int met
   const size_t lds_g_off = align_up(((size_t)meta_rows * kTileN + 1) * (gated ? 8 : 4), 16);
   size_t meta_bytes = meta_rows ? lds_g_off + (size_t)((K + 127) / 128) * 256 : 0;
   if (meta_bytes > kLdsMax - red || meta_rows > 1024) {
-    meta = kMetaRowGlobal;
-    meta_rows = 0;
-    meta_bytes = 0;
+    // the entries alone, and the groups from global memory (K past 61,000 at G
+    // = 128); else the metadata too
+    meta = lds_g_off <= kLdsMax - red ? kMetaRowLdsIdx : kMetaRowGlobal;
+    if (meta == kMetaRowGlobal) meta_rows = 0;
+    meta_bytes = meta_rows ? lds_g_off : 0;
   }
-  if (meta == kMetaRowGlobal && nw > 8) nw = 8;  // its metadata in registers: 16 waves would spill
+  // groups or metadata in registers: 16 waves would spill
+  if ((meta == kMetaRowLdsIdx || meta == kMetaRowGlobal) && nw > 8) nw = 8;
   // padded X + the zero entry + a spare entry
   const size_t x_bytes = ((size_t)M * 16 * ((K + 127) / 128) + 2) * 16;
   // the gather's copy of X + spare: row-major, or column-major with four
@@ -174,7 +177,7 @@ bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int met
   // M <= 2 they are even)
   const bool wide_pref = layout == TPDQ_LAYOUT_TILED && meta == kMetaGroup && !gated &&
                          (int64_t)K * N >= kWideMinWeights && M >= 3;
-  const bool small_m = meta != kMetaGroup || M <= 4;
+  const bool small_m = meta == kMetaGroup ? M <= 4 : meta != kMetaRowLdsIdx;
   const bool fits = meta_bytes + x_bytes <= budget && small_m && !wide_pref;
   int am;
   if (operand == kOperandGather) {

@@ -171,8 +171,8 @@ __device__ __forceinline__ u4_t dequant_rows(const UnpackConsts<DT>& k, uint32_t
   }
 }
 
-// dequant_rows on metadata entries e[r] = scale bits | (0x6400 | z) << 16:
-// two byte permutes make the zero pair (fp16 1024 + z) and the scale pair of
+// dequant_rows on metadata entries e[r] = scale bits | z << 16 (fp16: 0x6400 |
+// z): two byte permutes make the zero pair (fp16 1024 + z) and the scale pair of
 // each packed value pair. The nibbles at bits 4 .. 7 land as 1024 + 16 q and
 // one FMA brings them to 1024 + q (64 + q + 960, exact), so that both kinds
 // take the same zero pair.
@@ -199,7 +199,7 @@ __device__ __forceinline__ u4_t dequant_entries(const UnpackConsts<DT>& k, uint3
     uint32_t z[8], s[8];
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
-      z[r] = (e[r] >> 16) & 0x1Fu;
+      z[r] = e[r] >> 16;
       s[r] = e[r] & 0xFFFFu;
     }
     return dequant_rows<NAT, DT>(k, w, z, s);

@@ -31,7 +31,8 @@ constexpr size_t kLdsMax = 160 * 1024;
 enum MetaMode {
   kMetaGroup = 0,      // sorted rows: one (scale, zero) per 32-row step, staged in LDS
   kMetaRowGlobal = 1,  // per row through g_idx, read from global memory (Fig. 1 as drawn)
-  kMetaRowLds = 2,     // per row through g_idx, tile metadata staged in LDS
+  kMetaRowLds = 2,     // per row through g_idx, tile metadata and the rows' groups staged in LDS
+  kMetaRowLdsIdx = 3,  // as kMetaRowLds, the rows' groups from global memory (plan_decode's choice)
 };
 // Where the A operand (activations) comes from.
 enum AMode {

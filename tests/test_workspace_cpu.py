@@ -138,3 +138,14 @@ def test_ordered_calls_ask_for_no_act_order_workspace(monkeypatch):
     ordered = sizes(True, tpdq.PATH_ORDERED)
     assert len(ordered) == 3 and ordered == sizes(False, tpdq.PATH_ORDERED)
     assert all(a > o for a, o in zip(sizes(True, tpdq.PATH_ACTORDER), ordered))
+
+
+@pytest.mark.parametrize("K,G", [(61440, 128), (65536, 128), (65536, 256), (81920, 256)])
+@pytest.mark.parametrize("op,M", [("gemm", 1), ("gemm", 16), ("gemm", 64), ("gated", 4)])
+def test_long_act_order_rows_keep_their_metadata_in_lds(record, K, G, op, M):
+    """No act-order call whose tile's scales and zeros fit LDS reads them row by
+    row from global memory (the third template argument)."""
+    (r,) = record([dict(op=op, M=M, K=K, N=256, N2=0 if op == "gemm" else 512, G=G, path="actorder")])
+    k = [l["kernel"] for l in r["launches"] if "k_rowmeta" in l["kernel"]][0]
+    assert k.split(",")[2].strip() in ("2", "3"), k
+    assert r["launches"][0]["lds"] <= 160 * 1024
