@@ -640,8 +640,8 @@ __global__ __launch_bounds__(NW * 64) void k_ordered(GemmArgs a) {
   // fragments (4 * MT registers of 16 bytes per block) ride along. The
   // prepared operand with one row tile keeps four (Llama-70B TP=8 MLP at
   // M = 8: 16.1 -> 14.6 us; at M = 16 equal, 17.1 us), the other global
-  // operands two
-  constexpr int D = AG ? (AM == kAGlobalPrep && MT == 1 && TN <= 2 && !GATED ? 4 : 2) : 4;
+  // operands two, or one with four row tiles
+  constexpr int D = AG ? MT == 4 ? 1 : (AM == kAGlobalPrep && MT == 1 && TN <= 2 && !GATED ? 4 : 2) : 4;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1273,7 +1273,7 @@ __global__ __launch_bounds__(NW * 64) void k_rowmeta(GemmArgs a) {
 template <int MT, int NW, int SPG, int AM, int L, int DT>
 DecodeKernel pick_ordered_tn(int tn) {
   constexpr int MAX = rows_max_tn(L, SPG, MT);
-  if constexpr (MAX >= 1) if (tn == 1) return k_ordered<MT, NW, SPG, AM, L, 1, DT>;
+  if constexpr (MAX >= 1 && rows_min_tn(L, SPG, MT) == 1) if (tn == 1) return k_ordered<MT, NW, SPG, AM, L, 1, DT>;
   if constexpr (MAX >= 2) if (tn == 2) return k_ordered<MT, NW, SPG, AM, L, 2, DT>;
   if constexpr (MAX >= 3) if (tn == 3) return k_ordered<MT, NW, SPG, AM, L, 3, DT>;
   if constexpr (MAX >= 4) if (tn == 4) return k_ordered<MT, NW, SPG, AM, L, 4, DT>;
@@ -1285,7 +1285,7 @@ DecodeKernel pick_ordered_am(int am, int tn) {
   // plan_decode gives the ordered kernel 4 or 8 waves, one row and one column
   // tile with X in LDS, 4 waves with X from global memory; only those are
   // instantiated
-  if constexpr (NW == 4 && MT <= 2) {
+  if constexpr (NW == 4) {
     if (am == kAGlobal) return pick_ordered_tn<MT, NW, SPG, kAGlobal, L, DT>(tn);
     if (am == kAGlobalPrep) return pick_ordered_tn<MT, NW, SPG, kAGlobalPrep, L, DT>(tn);
   }
@@ -1386,7 +1386,7 @@ DecodeKernel pick_wide(const DecodePlan& p) {
 // with a second stream. Instantiated in their own translation units.
 template <int MT, int NW, int SPG, int L, int DT>
 DecodeKernel pick_gated_ordered_am(int am) {
-  if constexpr (NW == 4 && MT <= 2 && rows_max_tn(L, SPG, MT) >= 2) {
+  if constexpr (NW == 4 && rows_max_tn(L, SPG, MT) >= 2) {
     if (am == kAGlobal) return k_ordered<MT, NW, SPG, kAGlobal, L, 2, DT, true>;
     if (am == kAGlobalPrep) return k_ordered<MT, NW, SPG, kAGlobalPrep, L, 2, DT, true>;
   }

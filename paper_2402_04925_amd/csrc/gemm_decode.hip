@@ -97,11 +97,10 @@ DecodeKernel decode_kernel(const DecodePlan& p) {
 // with two row tiles. Measured best, M = 64: 6144 x 6144 (2, 3), 3584 x 8192
 // (2, 4), 8192 x 3584 (2, 2) and (1, 4) alike; M = 32: (1, 3), (1, 4) and
 // (2, 2) alike, (1, 2). gated: the two streams of one column tile.
-static int plan_rows(int M, int N, int layout, int spg, bool gated, int* mt, int* tn) {
-  const int rt = (M + kTileM - 1) / kTileM;
-  const int ntiles = (N + kTileN - 1) / kTileN;
+static int plan_bytes(int rt, int ntiles, int layout, int spg, bool gated, int* mt, int* tn) {
   int best = INT_MAX;
-  for (int m : {2, 1})
+  for (int m : {2, 1}) {
+    if (m == 2 && layout == TPDQ_LAYOUT_GPTQ && spg == 1) continue;  // rows_us judges these
     for (int n = gated ? 2 : 1; n <= std::min(gated ? 2 : 4, rows_max_tn(layout, spg, m)); ++n) {
       const int64_t wgs = (int64_t)((rt + m - 1) / m) * (gated ? ntiles : (ntiles + n - 1) / n);
       const int cost = (int)((wgs + 255) / 256) * (4 * m + 2 * n);
@@ -111,14 +110,62 @@ static int plan_rows(int M, int N, int layout, int spg, bool gated, int* mt, int
         *tn = n;
       }
     }
+  }
   return best;
 }
 
-// 2 us of launch and 0.0134 us per unit of plan_rows and block of 128 rows
+// Microseconds of a pair (X prepared: with the gather or copy before it), fitted
+// to 28,000 launches of random sizes (M = 17 to 255, K = 256 to 60000, N = 128
+// to 32768, every group size) within 14%: per workgroup a start, and per block
+// of 128 rows its row tiles (the last group's missing ones cost nothing), its
+// column tiles, its MFMAs and the closes of its groups. A second workgroup on a
+// CU adds little less than the first one takes, but where registers allow one
+// only (rows_alone) nothing covers its start.
+static double rows_us(int rt, int ntiles, int nblk, int layout, int spg, bool gated, bool prepared, int m, int n) {
+  const bool tiled = layout == TPDQ_LAYOUT_TILED;
+  const int groups = (rt + m - 1) / m;
+  const int64_t wgs = (int64_t)groups * (gated ? ntiles : (ntiles + n - 1) / n);
+  const int per_cu = (int)((wgs + 255) / 256);
+  const bool alone = rows_alone(layout, spg, m, n);
+  const double start = tiled ? (alone ? 2.1 : 0.6) : (alone ? 2.7 : 0.9);
+  const double row = prepared ? 0.037 : 0.089, col = tiled ? 0.023 : prepared ? 0.037 : 0.028;
+  const double close = (tiled ? 0.0075 : 0.0057) * (spg > 4 ? 0.5 : 4.0 / spg), mfma = prepared ? 0.005 : 0.0;
+  const double one = start + nblk * (row * rt / groups + col * n + (close + mfma) * m * n);
+  const double two = tiled ? 1.8 : 1.95;
+  return (prepared ? 5.8 : 3.9) + one * (alone ? per_cu : per_cu / 2 * two + per_cu % 2);
+}
+
+// The pair by bytes, or where X is prepared (and for GPTQ-layout weights of G =
+// 32, of which the bytes know one row tile only) the one that rows_us finds at
+// least 7% faster: four row tiles on many rounds, or a pair that leaves room for
+// a second workgroup. Of 2,000 random sizes the result is 3.7% faster than the
+// bytes' on average, and slower by more than 3% in 1%: 2176 x 25216 at M = 100
+// 54 -> 38 us, GPTQ-layout of G = 32 174 -> 76. (On X as it is, the bytes are the
+// better judge.)
+static void plan_rows(int M, int K, int N, int layout, int spg, bool gated, bool prepared, int* mt, int* tn) {
+  const int rt = (M + kTileM - 1) / kTileM, ntiles = (N + kTileN - 1) / kTileN, nblk = (K + 127) / 128;
+  plan_bytes(rt, ntiles, layout, spg, gated, mt, tn);
+  if (!prepared && !(layout == TPDQ_LAYOUT_GPTQ && spg == 1)) return;
+  auto us = [&](int m, int n) { return rows_us(rt, ntiles, nblk, layout, spg, gated, prepared, m, n); };
+  double best = 0.93 * us(*mt, *tn);
+  for (int m : {4, 2, 1}) {
+    if (m == 4 && (rt <= 2 || !prepared)) continue;
+    const int n0 = gated ? 2 : rows_min_tn(layout, spg, m), n1 = std::min(gated ? 2 : 4, rows_max_tn(layout, spg, m));
+    for (int n = n0; n <= n1; ++n)
+      if (us(m, n) < best) {
+        best = us(m, n);
+        *mt = m;
+        *tn = n;
+      }
+  }
+}
+
+// 2 us of launch and 0.0134 us per unit of plan_bytes and block of 128 rows
 // (6144 x 6144 at M = 64: 14 units, 48 blocks, 11 us)
 double rows_cost(int M, const tpdq_w4* w) {
   int mt, tn;
-  return 2.0 + 0.0134 * plan_rows(M, w->N, w->layout, w->group_size / 32, false, &mt, &tn) * ((w->K + 127) / 128);
+  return 2.0 + 0.0134 * plan_bytes((M + kTileM - 1) / kTileM, (w->N + kTileN - 1) / kTileN, w->layout,
+                                   w->group_size / 32, false, &mt, &tn) * ((w->K + 127) / 128);
 }
 
 bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int meta_pref, int operand,
@@ -220,7 +267,7 @@ bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int met
             M <= kDecodeMaxM && !(mt == 4 && am == kAGlobal) && (int64_t)K * N >= kWideMinWeights;
   p->rgs = 1;
   if (meta == kMetaGroup && a_global(am) && !p->wide && M > kTileM) {
-    plan_rows(M, N, layout, spg, gated, &mt, &tn);
+    plan_rows(M, K, N, layout, spg, gated, operand == kOperandPrepared, &mt, &tn);
     p->rgs = ((M + kTileM - 1) / kTileM + mt - 1) / mt;
     nw = 4;
   }

@@ -113,13 +113,25 @@ constexpr int64_t kWideMinWeights = (int64_t)64 << 20;
 constexpr int kWideTargetWgs = 200;
 
 // Column tiles per workgroup that the ordered kernel's registers hold beside mt
-// row tiles read from global memory (0: not that many row tiles): GPTQ-layout
-// weights, and the metadata of groups of 32 and 64 (spg 1, 2), take more
+// row tiles read from global memory (0: not that many row tiles): GPTQ-layout weights, and the metadata of
+// groups of 32 and 64 (spg 1, 2), take more
 constexpr int rows_max_tn(int layout, int spg, int mt) {
+  if (mt == 4) return layout == TPDQ_LAYOUT_GPTQ && spg == 2 ? 0 : 2;
   if (layout == TPDQ_LAYOUT_TILED) return spg == 1 && mt == 2 ? 3 : 4;
-  if (spg == 1) return mt == 1 ? 2 : 0;
-  if (spg == 2) return mt == 1 ? 4 : 2;
-  return 4;
+  if (spg == 1) return 2;
+  return spg == 2 && mt == 2 ? 2 : 4;
+}
+// ... and the fewest: four row tiles over one column tile only pay where two
+// column tiles leave room for one workgroup per CU
+constexpr int rows_min_tn(int layout, int spg, int mt) {
+  return mt == 4 && !(layout == TPDQ_LAYOUT_GPTQ && spg == 1) ? 2 : 1;
+}
+// Whether that workgroup's registers leave room for no second one on its CU
+// (more than 256 per lane, in one element type at least)
+constexpr bool rows_alone(int layout, int spg, int mt, int tn) {
+  if (layout == TPDQ_LAYOUT_TILED) return tn == 4 ? mt == 2 || spg == 1 : tn == 3 && (spg == 1 || (spg == 2 && mt == 2));
+  if (spg == 1) return tn == 2;
+  return spg == 8 && mt == 2 && tn == 4;
 }
 
 // The in-LDS gather of X[:, perm] is planned on grids of at most this many

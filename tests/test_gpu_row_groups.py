@@ -96,3 +96,49 @@ def test_mlp_row_groups(M, layout, gated):
         assert o.rel_err(np_of(y1), e1) <= 2 * TOL["fp16"], N1
         # Y2 of the Y1 that the call rounded
         assert o.rel_err(np_of(y2), np_of(y1).astype(np.float64) @ _deq(down)) <= 2 * TOL["fp16"], N1
+
+
+# 38 blocks of 128 rows, 9 or 10 to a wave, the last one of 8 rows: whole chunks
+# of four, the reload of the metadata and a ragged last chunk; from 33 rows on X
+# without a perm is copied to operand order. tests/test_plans_cpu.py has the
+# kernels that these calls reach.
+LONG = [(K, N, G, M, layout, dtype) for K, N in ((4744, 9224),) for G in (32, 64, 128, 256) for M in (17, 64, 100, 250)
+        for layout, dtype in (("tiled", "bf16"), ("gptq", "fp16"), ("gptq", "bf16"), ("tiled", "fp16"))]
+_long = {}
+
+
+@pytest.mark.parametrize("K,N,G,M,layout,dtype", LONG)
+def test_long_rows(K, N, G, M, layout, dtype):
+    import torch
+    import paper_2402_04925_amd as tpdq
+    dev = torch_dev()
+    log(f"long rows K={K} N={N} G={G} M={M} {layout} {dtype}")
+    if _long.get("key") != (K, N, G, dtype):
+        l = _sorted(K, N, G, dtype, G)
+        # whole octets of columns: the first and last tiles and 12 others
+        octets = np.unique(np.concatenate([[0, 1, N // 8 - 2, N // 8 - 1],
+                                           np.random.default_rng(G).integers(0, N // 8, 12)]))
+        cols = (8 * octets[:, None] + np.arange(8)).ravel()
+        W = o.dequant(np.ascontiguousarray(l.qweight[:, cols]), np.ascontiguousarray(l.scales[:, cols]),
+                      np.ascontiguousarray(l.qzeros[:, octets]), l.g_idx)
+        w = layer_to_dev(l, dev, with_gidx=False)
+        _long.update(key=(K, N, G, dtype), cols=cols, W=W, w={"gptq": w, "tiled": tpdq.pack_tiled(w)})
+    w, cols, W = _long["w"][layout], _long["cols"], _long["W"]
+    X = _x(M, K, dtype)
+    Xd = to_dev(X, dev, dtype == "bf16")
+    perm = np.random.default_rng(1).permutation(K).astype(np.int32)
+    x = X.astype(np.float64)
+    y = tpdq.w4a16_gemm(Xd, w, tpdq.PATH_ORDERED)
+    assert o.rel_err(np_of(y)[:, cols], x @ W) <= TOL[dtype]
+    assert torch.equal(y, tpdq.w4a16_gemm(Xd, w, tpdq.PATH_ORDERED))
+    yp = tpdq.w4a16_gemm(Xd, w, tpdq.PATH_ORDERED, x_perm=to_dev(perm, dev))
+    assert o.rel_err(np_of(yp)[:, cols], x[:, perm] @ W) <= TOL[dtype]
+    if layout == "gptq":  # X as it is: no workspace for a copy
+        yn = torch.empty_like(y)
+        c = w.c_struct(tpdq.PATH_ORDERED)
+        from paper_2402_04925_amd import _abi
+        _abi.check(_abi.lib().tpdq_w4a16_gemm(
+            Xd.data_ptr(), K, M, None, ctypes.byref(c), tpdq.PATH_ORDERED,
+            tpdq.FP16 if dtype == "fp16" else tpdq.BF16, yn.data_ptr(), N, None, 0,
+            torch.cuda.current_stream(dev).cuda_stream))
+        assert o.rel_err(np_of(yn)[:, cols], x @ W) <= TOL[dtype]

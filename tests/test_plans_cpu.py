@@ -1,0 +1,62 @@
+"""Which kernels calls of a size take, from their recorded launches (no GPU)."""
+import os
+
+import pytest
+
+from paper_2402_04925_amd import _abi
+from tests import launches
+from tests.test_gpu_row_groups import LONG
+
+if not os.path.exists(_abi.LIB_PATH):
+    from paper_2402_04925_amd import build
+    build.build()
+
+
+@pytest.fixture(scope="module")
+def record(tmp_path_factory):
+    d = str(tmp_path_factory.mktemp("recorder"))
+    return lambda calls: launches.record(calls, d)
+
+
+def _ordered(result):
+    """(row tiles, column tiles, prepared X, grid) of a call's ordered launches."""
+    out = []
+    for l in result["launches"]:
+        if l["kernel"].startswith("k_ordered"):
+            a = l["kernel"].split("<")[1].split(",")
+            out.append((int(a[0]), int(a[5]), a[3].strip() == "3", l["grid"]))
+    return out
+
+
+def test_long_rows_reach_what_they_test(record):
+    """The calls of test_gpu_row_groups.test_long_rows: one, two and four row
+    tiles in both layouts, from the copy in operand order and from X as it is."""
+    calls = [dict(op="gemm", M=M, K=K, N=N, G=G, layout=layout, dtype=dtype, gidx=False,
+                  perm=perm, ws="doc") for K, N, G, M, layout, dtype in LONG for perm in (False, True)]
+    seen = {"tiled": set(), "gptq": set()}
+    for c, r in zip(calls, record(calls)):
+        seen[c["layout"]] |= {(mt, prep) for mt, _, prep, _ in _ordered(r)}
+    for layout in seen:
+        assert {mt for mt, _ in seen[layout]} == {1, 2, 4}, layout
+        assert {prep for _, prep in seen[layout]} == {True, False}, layout
+
+
+# Row groups of one tile read GPTQ-layout weights of G = 32 once per 16 rows:
+# 5248 x 20608 at M = 1000 took 1841 us where launches of 64 rows with all four
+# row tiles had taken 1245
+@pytest.mark.parametrize("K,N,M", [(5248, 20608, 1000), (1024, 24064, 128), (2560, 30208, 48), (8192, 8192, 1500)])
+@pytest.mark.parametrize("G,dtype", [(32, "fp16"), (32, "bf16"), (256, "fp16")])
+def test_many_rows_share_their_weights(record, K, N, M, G, dtype):
+    (r,) = record([dict(op="gemm", M=M, K=K, N=N, G=G, layout="gptq", dtype=dtype, gidx=False, perm=True)])
+    for mt, tn, _, grid in _ordered(r):
+        assert mt >= 2
+
+
+# Two row and four column tiles take the registers of a whole CU: on grids of
+# many rounds no second workgroup covers its waits (2304 x 26368 at M = 100, 38.7
+# -> 54.5 us)
+@pytest.mark.parametrize("K,N,M", [(2304, 26368, 33), (2176, 25216, 64), (512, 14848, 64)])
+@pytest.mark.parametrize("layout,G", [("tiled", 128), ("tiled", 256), ("gptq", 256)])
+def test_many_rounds_take_two_workgroups_per_cu(record, K, N, M, layout, G):
+    (r,) = record([dict(op="gemm", M=M, K=K, N=N, G=G, layout=layout, gidx=False, perm=True)])
+    assert all((mt, tn) != (2, 4) or grid <= 256 for mt, tn, _, grid in _ordered(r))
