@@ -134,6 +134,17 @@ bool rows_copy(int M, const tpdq_w4* w, size_t avail) {
          avail >= prepared_bytes(std::min(M, kRowsMaxM), w->K);
 }
 
+// 17 to 64 rows of X as it is on few columns and long rows: the row groups leave
+// most CUs idle, so K is split (the wide kernel; the workspace such a call has
+// to bring holds its partials). Wide against row groups on 260 random tiled
+// weights of 16M to 64M elements, by K, at M = 17 / 32 / 64: from 8192 0.88 /
+// 0.94 / 1.01, 12288 0.84 / 0.90 / 0.96, 16384 0.75 / 0.81 / 0.91, 30000 0.52 /
+// 0.55 / 0.68.
+bool long_rows(int M, const tpdq_w4* w, int meta) {
+  return meta == kMetaGroup && step_groups(w->group_size) && w->layout == TPDQ_LAYOUT_TILED && M > kTileM &&
+         M <= kDecodeMaxM && w->K >= 12288 && (int64_t)w->K * w->N >= ((int64_t)16 << 20);
+}
+
 // Rows of one launch of the decode kernels (the last launch of a call may have
 // fewer).
 int chunk_rows(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, size_t avail) {
@@ -190,10 +201,15 @@ bool dense_for(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, bool g
 // per-row metadata from 12 on weights of 16M elements. 6144 x 6144 act-order
 // GEMM with the copy: M = 64 59.7 -> 38.1 us, M = 32 33.0 -> 24.4, M = 16 23.7
 // -> 20.8; 2048 x 2048 at M = 16 8.9 -> 8.6, M = 8 7.3 -> 8.5.
+// whole: the launch is the whole call (its X rows lie as the call's bound on the
+// workspace assumes).
 bool decode_plan_for(int mc, bool perm, const tpdq_w4* w, int meta, int dt, DecodePlan* plan,
-                     bool* prepared, bool gated, bool* plain, size_t avail) {
+                     bool* prepared, bool gated, bool* plain, size_t avail, bool whole) {
   *prepared = false;
   if (plain) *plain = false;
+  if (!perm && !gated && whole && long_rows(mc, w, meta))
+    return plan_decode(mc, w->K, w->N, w->group_size, w->num_groups, w->layout, meta, kOperandPlain, dt, plan,
+                       false, true);
   const bool copy = meta == kMetaGroup && step_groups(w->group_size)
                         ? mc > kTileM && rows_route(mc, false, w, meta, avail) && rows_copy(mc, w, avail)
                         : mc > kTileM || (mc >= 12 && (int64_t)w->K * w->N >= ((int64_t)16 << 20));
@@ -263,7 +279,7 @@ size_t gemm_ws_need(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, i
     if (mc == 0) continue;
     DecodePlan dp;
     bool prepared = false;
-    if (!decode_plan_for(mc, perm, w, meta, dt, &dp, &prepared, gated, nullptr, avail)) {
+    if (!decode_plan_for(mc, perm, w, meta, dt, &dp, &prepared, gated, nullptr, avail, mc == M)) {
       if (perm) need = std::max(need, decode_gather_bytes(M, w->K));
       continue;
     }
@@ -365,7 +381,7 @@ tpdq_status run_gemm(const uint16_t* X, int64_t ldx, int M, const int32_t* perm,
                         ? plan_decode(mc, w->K, w->N, w->group_size, w->num_groups, w->layout, meta,
                                       kOperandPrepared, dt, &plan, gated)
                         : decode_plan_for(mc, perm != nullptr, w, meta, dt, &plan, &prepared, gated,
-                                          &plain, avail);
+                                          &plain, avail, mc == M);
     const int operand =
         prepared ? kOperandPrepared : (perm && !plain ? kOperandGather : kOperandPlain);
     if (ok && plain) {
@@ -444,9 +460,10 @@ bool mlp_prepared_y1(int M, int64_t ldx, bool perm, const tpdq_w4* w1, const tpd
   }
   DecodePlan p1, p2;
   bool prepared = false;
-  if (!decode_plan_for(M, perm, w1, meta, dt, &p1, &prepared, gated, nullptr, kBaseWs) || p1.wide) return false;
+  if (!decode_plan_for(M, perm, w1, meta, dt, &p1, &prepared, gated, nullptr, kBaseWs, true) || p1.wide)
+    return false;
   // GEMM2 would read row-major Y1 from global memory through the tile kernel
-  if (!decode_plan_for(M, false, w2, meta, dt, &p2, &prepared, false, nullptr, kBaseWs) || p2.wide ||
+  if (!decode_plan_for(M, false, w2, meta, dt, &p2, &prepared, false, nullptr, kBaseWs, false) || p2.wide ||
       p2.amode != kAGlobal)
     return false;
   DecodePlan p3;

@@ -1374,8 +1374,8 @@ DecodeKernel pick_wide(const DecodePlan& p) {
   switch (p.mt) {
     case 1: return prep ? pick_wide_spg<1, 1, true, DT>(p.spg) : pick_wide_spg<1, 1, false, DT>(p.spg);
     case 2: return prep ? pick_wide_spg<2, 1, true, DT>(p.spg) : pick_wide_spg<2, 1, false, DT>(p.spg);
-    // a gather whose row is past the M-tiled kernel's LDS
-    case 4: return prep ? pick_wide_spg<4, 1, true, DT>(p.spg) : nullptr;
+    // long rows, or a gather whose row is past the M-tiled kernel's LDS
+    case 4: return prep ? pick_wide_spg<4, 1, true, DT>(p.spg) : pick_wide_spg<4, 1, false, DT>(p.spg);
   }
   return nullptr;
 }

@@ -1,7 +1,7 @@
 """GPU wide decode kernel (ordered path, tiled weights of at least 64M
-elements, or of 16M with row-major X and M > 16; X too large to stage whole in LDS: 8 waves over 128 columns share
-the activations through LDS, K split over workgroups when the columns alone
-give too few) against the oracle on sampled columns."""
+elements, or of 16M with row-major X, M > 16 and K >= 12288: X too large to
+stage whole in LDS, 8 waves over 128 columns share the activations through LDS,
+K split over workgroups when the columns alone give too few) against the oracle on sampled columns."""
 import numpy as np
 import pytest
 
@@ -17,10 +17,13 @@ pytestmark = pytest.mark.gpu
 SHAPES = [
     (8192, 8192, 128, 8), (8192, 8200, 64, 16), (4096, 16384, 32, 17), (16384, 4096, 256, 32),
     (8192, 28672, 128, 12),
-    # 16M to 64M elements: row-major X with two or more row tiles only
+    # 16M to 64M elements with two or more row tiles: row groups
     (8192, 3584, 128, 32), (3584, 8192, 128, 64), (6144, 6144, 128, 40),
     # 64M elements at M = 3 and 4, where X would fit in LDS (wide from 3 rows on)
     (8192, 8192, 128, 3), (8192, 8192, 128, 4),
+    # long rows of 16M to 64M elements: the wide kernel on row-major X, row groups
+    # after a gather; ragged N, a partial last group and block
+    (12288, 1544, 32, 64), (16392, 1032, 64, 33), (16384, 1160, 256, 17), (34816, 512, 128, 48),
 ]
 
 

@@ -60,3 +60,15 @@ def test_many_rows_share_their_weights(record, K, N, M, G, dtype):
 def test_many_rounds_take_two_workgroups_per_cu(record, K, N, M, layout, G):
     (r,) = record([dict(op="gemm", M=M, K=K, N=N, G=G, layout=layout, gidx=False, perm=True)])
     assert all((mt, tn) != (2, 4) or grid <= 256 for mt, tn, _, grid in _ordered(r))
+
+
+# 17 to 64 rows on few columns: row groups over the whole K left most CUs idle
+# (65536 x 288 at M = 17, 27 -> 62 us)
+@pytest.mark.parametrize("K,N,G", [(65536, 288, 256), (34816, 512, 32), (12288, 4096, 128)])
+@pytest.mark.parametrize("M", [17, 33, 64])
+def test_long_rows_are_split(record, K, N, G, M):
+    call = dict(op="gemm", M=M, K=K, N=N, G=G, gidx=False)
+    r, null = record([call, dict(call, ws=None)])
+    kernels = [l["kernel"].split("<")[0] for l in r["launches"]]
+    assert kernels == ["k_wide", "k_splitk_reduce"] and launches.outside(r) == []
+    assert null["status"] == _abi.ERR_WORKSPACE  # as documented: M > 16 and K >= N
