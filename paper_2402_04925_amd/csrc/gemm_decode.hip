@@ -135,17 +135,18 @@ static double rows_us(int rt, int ntiles, int nblk, int layout, int spg, bool ga
   return (prepared ? 5.8 : 3.9) + one * (alone ? per_cu : per_cu / 2 * two + per_cu % 2);
 }
 
-// The pair by bytes, or where X is prepared (and for GPTQ-layout weights of G =
-// 32, of which the bytes know one row tile only) the one that rows_us finds at
-// least 7% faster: four row tiles on many rounds, or a pair that leaves room for
-// a second workgroup. Of 2,000 random sizes the result is 3.7% faster than the
+// The pair by bytes, or where X is prepared the one that rows_us finds at least
+// 7% faster: four row tiles on many rounds, or a pair that leaves room for a
+// second workgroup. Of 2,000 random sizes the result is 3.7% faster than the
 // bytes' on average, and slower by more than 3% in 1%: 2176 x 25216 at M = 100
-// 54 -> 38 us, GPTQ-layout of G = 32 174 -> 76. (On X as it is, the bytes are the
-// better judge.)
+// 54 -> 38 us, GPTQ-layout of G = 32 174 -> 76. On X as it is the bytes are the
+// better judge, but know one row tile only for GPTQ-layout weights of G = 32: two
+// of these pay up to 32 rows on K of 4096 or more (13944 x 5992 at M = 32 51 -> 44
+// us; 1664 x 12544 16.9 -> 18.1).
 static void plan_rows(int M, int K, int N, int layout, int spg, bool gated, bool prepared, int* mt, int* tn) {
   const int rt = (M + kTileM - 1) / kTileM, ntiles = (N + kTileN - 1) / kTileN, nblk = (K + 127) / 128;
   plan_bytes(rt, ntiles, layout, spg, gated, mt, tn);
-  if (!prepared && !(layout == TPDQ_LAYOUT_GPTQ && spg == 1)) return;
+  if (!prepared && !(layout == TPDQ_LAYOUT_GPTQ && spg == 1 && rt <= 2 && K >= 4096)) return;
   auto us = [&](int m, int n) { return rows_us(rt, ntiles, nblk, layout, spg, gated, prepared, m, n); };
   double best = 0.93 * us(*mt, *tn);
   for (int m : {4, 2, 1}) {

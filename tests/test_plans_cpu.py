@@ -72,3 +72,12 @@ def test_long_rows_are_split(record, K, N, G, M):
     kernels = [l["kernel"].split("<")[0] for l in r["launches"]]
     assert kernels == ["k_wide", "k_splitk_reduce"] and launches.outside(r) == []
     assert null["status"] == _abi.ERR_WORKSPACE  # as documented: M > 16 and K >= N
+
+
+def test_short_rows_keep_their_pair(record):
+    """GPTQ-layout weights of G = 32 under X as it is: the pair by bytes (1024 x
+    10368 at M = 33 14 us; two row tiles, one workgroup per CU, 21)."""
+    calls = [dict(op="gemm", M=M, K=K, N=N, G=32, layout="gptq", gidx=False)
+             for K, N, M in ((1024, 10368, 33), (384, 6912, 48), (512, 7680, 65))]
+    for r in record(calls):
+        assert [mt for mt, _, _, _ in _ordered(r)] == [1]
