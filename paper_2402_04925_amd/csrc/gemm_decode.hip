@@ -97,7 +97,7 @@ DecodeKernel decode_kernel(const DecodePlan& p) {
 // with two row tiles. Measured best, M = 64: 6144 x 6144 (2, 3), 3584 x 8192
 // (2, 4), 8192 x 3584 (2, 2) and (1, 4) alike; M = 32: (1, 3), (1, 4) and
 // (2, 2) alike, (1, 2). gated: the two streams of one column tile.
-static int plan_bytes(int rt, int ntiles, int layout, int spg, bool gated, int* mt, int* tn) {
+static void plan_bytes(int rt, int ntiles, int layout, int spg, bool gated, int* mt, int* tn) {
   int best = INT_MAX;
   for (int m : {2, 1}) {
     if (m == 2 && layout == TPDQ_LAYOUT_GPTQ && spg == 1) continue;  // rows_us judges these
@@ -111,7 +111,6 @@ static int plan_bytes(int rt, int ntiles, int layout, int spg, bool gated, int* 
       }
     }
   }
-  return best;
 }
 
 // Microseconds of a pair (X prepared: with the gather or copy before it), fitted
@@ -161,12 +160,13 @@ static void plan_rows(int M, int K, int N, int layout, int spg, bool gated, bool
   }
 }
 
-// 2 us of launch and 0.0134 us per unit of plan_bytes and block of 128 rows
-// (6144 x 6144 at M = 64: 14 units, 48 blocks, 11 us)
-double rows_cost(int M, const tpdq_w4* w) {
+// With X prepared the gather or copy counts too.
+double rows_cost(int M, const tpdq_w4* w, bool prepared) {
+  const int spg = w->group_size / 32;
   int mt, tn;
-  return 2.0 + 0.0134 * plan_bytes((M + kTileM - 1) / kTileM, (w->N + kTileN - 1) / kTileN, w->layout,
-                                   w->group_size / 32, false, &mt, &tn) * ((w->K + 127) / 128);
+  plan_rows(M, w->K, w->N, w->layout, spg, false, prepared, &mt, &tn);
+  return rows_us((M + kTileM - 1) / kTileM, (w->N + kTileN - 1) / kTileN, (w->K + 127) / 128, w->layout, spg, false,
+                 prepared, mt, tn);
 }
 
 bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int meta_pref, int operand,

@@ -521,18 +521,39 @@ __global__ __launch_bounds__(256) void k_gather_rows(const uint16_t* __restrict_
 }  // namespace
 
 // Microseconds of one M-tiled launch by shape: workgroups run in rounds of one
-// per CU, each over nblk / ks blocks of 128 rows; split partials are written
-// once and read once by the reduce. Per block and round, measured on 6144 x
-// 6144, 8192 x 3584 and 3584 x 8192 at M = 300 to 1500: 128 x 512 tiles 2.8 us
-// (bf16 3.2), 64 x 512 tiles 1.9 us (bf16 2.5), about 4 us of prologue and
-// epilogue; partials at 4.5 TB/s plus a 4 us launch.
-static double mtile_cost(int M, int N, int nblk, int rt, int ks, bool gated, int dt) {
+// per CU, each over nblk / ks blocks of 128 rows (start + block us a round); split
+// partials are written once and read once by the reduce (at mb bytes per us).
+static double tiles_us(int M, int N, int nblk, int rt, int ks, bool gated, double start, double block,
+                       double reduce, double mb) {
   const int bn = gated ? 256 : 512;
   const int64_t wgs = (int64_t)((M + 16 * rt - 1) / (16 * rt)) * ((N + bn - 1) / bn) * ks;
-  const double tb = dt == kBF16 ? (rt == 8 ? 3.2 : 2.5) : (rt == 8 ? 2.8 : 1.9);
   const double rounds = (double)((wgs + kMtileSlots - 1) / kMtileSlots);
-  const double part = ks > 1 ? 4.0 + (double)ks * M * N * (gated ? 16.0 : 8.0) / 4.5e6 : 0.0;
-  return rounds * (4.0 + tb * ((nblk + ks - 1) / ks)) + part;
+  const double part = ks > 1 ? reduce + (double)ks * M * N * (gated ? 16.0 : 8.0) / mb : 0.0;
+  return rounds * (start + block * ((nblk + ks - 1) / ks)) + part;
+}
+
+// The tile and split at prefill sizes. Measured on 6144 x 6144, 8192 x 3584 and
+// 3584 x 8192 at M = 300 to 1500 with G = 128, per block 128 x 512 tiles 2.8 us
+// (bf16 3.2), 64 x 512 ones 1.9 (2.5). Groups of 32 and 64 make the 64-row tiles
+// dearer (prefill_us has the figures) and are not counted here: by time alone
+// some of their sizes would take 128-row tiles, whose weights are rounded, where
+// they have exact ones now (3584 x 8192, bf16, G = 32, M = 1000: 106 us exact, 78
+// rounded).
+static double mtile_cost(int M, int N, int nblk, int rt, int ks, bool gated, int dt) {
+  const double tb = dt == kBF16 ? (rt == 8 ? 3.2 : 2.5) : (rt == 8 ? 2.8 : 1.9);
+  return tiles_us(M, N, nblk, rt, ks, gated, 4.0, tb, 4.0, 4.5e6);
+}
+
+// With the group size, where the choice is between kernels of one precision:
+// fitted within 3.3% to 530 GEMMs of those sizes and 4096 x 11008 at M = 100 to
+// 1500. Exact 64-row tiles close every group; rounded 128-row ones load its
+// metadata and spill.
+static double prefill_us(int M, int N, int nblk, int rt, int ks, bool gated, int dt, int spg) {
+  // G = 32, 64, 128, 256
+  static constexpr double block[2][2][4] = {{{2.6, 2.1, 1.7, 1.75}, {3.95, 3.75, 2.7, 2.7}},
+                                            {{3.2, 2.4, 2.0, 1.95}, {3.5, 3.65, 3.1, 3.1}}};
+  const double tb = block[dt == kBF16][rt == 8][spg == 1 ? 0 : spg == 2 ? 1 : spg == 4 ? 2 : 3];
+  return tiles_us(M, N, nblk, rt, ks, gated, 7.7, tb, 2.8, 8.8e6);
 }
 
 bool plan_mtile(int M, int64_t ldx, const tpdq_w4* w, int meta, int dt, bool gated, bool optional,
@@ -580,10 +601,13 @@ bool plan_mtile(int M, int64_t ldx, const tpdq_w4* w, int meta, int dt, bool gat
     *p = cut(4);
     // more than one 64-row tile: 128-row tiles halve the activations' share of
     // a CU's bytes, for twice the partials (8192 x 28672 and 28672 x 8192 at M
-    // = 128: 84.8 and 81.9 us -> 77.1 and 76.7)
+    // = 128: 84.8 and 81.9 us -> 77.1 and 76.7), not over few columns, where the
+    // splits are many (53248 x 2048, G = 64, at M = 160 68 -> 80)
     if (M > 64 && optional) {
       const MtilePlan c = cut(8);
-      if (mtile_part_bytes(c, M, N) <= part_budget) *p = c;
+      if (mtile_part_bytes(c, M, N) <= part_budget &&
+          prefill_us(M, N, nblk, 8, c.ks, false, dt, spg) < prefill_us(M, N, nblk, 4, p->ks, false, dt, spg))
+        *p = c;
     }
     return true;
   }
@@ -612,7 +636,8 @@ bool plan_mtile(int M, int64_t ldx, const tpdq_w4* w, int meta, int dt, bool gat
         if (ks > 1 && (!optional || mtile_part_bytes(c, M, N) > budget ||
                        (int64_t)ks * M * N * (gated ? 8 : 4) >= lim))
           break;
-        const double cost = mtile_cost(M, N, nblk, rt, ks, gated, dt);
+        const double cost = M < kPrefillMinM ? prefill_us(M, N, nblk, rt, ks, gated, dt, spg)
+                                             : mtile_cost(M, N, nblk, rt, ks, gated, dt);
         if (cost < 0.98 * best) {
           best = cost;
           c.cost = cost;

@@ -181,11 +181,11 @@ struct MtilePlan {
   bool gated;          // Y = silu(X W) * (X W_up)
   double cost;         // exact plans: microseconds by the planner's model
 };
+// Microseconds of the ordered kernel's row groups at M rows on this weight
+double rows_cost(int M, const tpdq_w4* w, bool prepared);
 // optional: also the plans that only serve as a faster route than another one
 // (exact, or a K split at prefill sizes), with partials of at most part_budget
 // bytes
-// Microseconds of the ordered kernel's row groups at M rows on this weight
-double rows_cost(int M, const tpdq_w4* w);
 bool plan_mtile(int M, int64_t ldx, const tpdq_w4* w, int meta, int dt, bool gated, bool optional,
                 size_t part_budget, MtilePlan* p);
 // workspace bytes of the fp32 partials (0 when ks == 1)

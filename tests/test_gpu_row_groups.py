@@ -98,12 +98,13 @@ def test_mlp_row_groups(M, layout, gated):
         assert o.rel_err(np_of(y2), np_of(y1).astype(np.float64) @ _deq(down)) <= 2 * TOL["fp16"], N1
 
 
-# 38 blocks of 128 rows, 9 or 10 to a wave, the last one of 8 rows: whole chunks
+# 38 (49) blocks of 128 rows, 9 to 13 to a wave, the last one ragged: whole chunks
 # of four, the reload of the metadata and a ragged last chunk; from 33 rows on X
 # without a perm is copied to operand order. tests/test_plans_cpu.py has the
 # kernels that these calls reach.
-LONG = [(K, N, G, M, layout, dtype) for K, N in ((4744, 9224),) for G in (32, 64, 128, 256) for M in (17, 64, 100, 250)
-        for layout, dtype in (("tiled", "bf16"), ("gptq", "fp16"), ("gptq", "bf16"), ("tiled", "fp16"))]
+LONG = [(K, N, G, M, layout, dtype) for K, N, G, M in
+        [(4744, 12296, G, M) for G in (32, 64, 128, 256) for M in (17, 64, 100, 250)] + [(6200, 4104, 128, 33)]
+        for dtype in ("fp16", "bf16") for layout in ("tiled", "gptq")]
 _long = {}
 
 
