@@ -134,15 +134,19 @@ bool rows_copy(int M, const tpdq_w4* w, size_t avail) {
          avail >= prepared_bytes(std::min(M, kRowsMaxM), w->K);
 }
 
-// 17 to 64 rows of X as it is on few columns and long rows: the row groups leave
-// most CUs idle, so K is split (the wide kernel; the workspace such a call has
-// to bring holds its partials). Wide against row groups on 260 random tiled
+// Rows of X as it is on tiled weights of 16M to 64M elements where the wide
+// kernel beats the row groups. 17 to 64 rows on few columns and long rows: the row
+// groups leave most CUs idle, so K is split (the workspace such a call has to
+// bring holds the partials). Wide against row groups on 260 random tiled
 // weights of 16M to 64M elements, by K, at M = 17 / 32 / 64: from 8192 0.88 /
 // 0.94 / 1.01, 12288 0.84 / 0.90 / 0.96, 16384 0.75 / 0.81 / 0.91, 30000 0.52 /
-// 0.55 / 0.68.
-bool long_rows(int M, const tpdq_w4* w, int meta) {
+// 0.55 / 0.68. And 33 to 64 rows on 25600 columns or more, 200 workgroups without
+// a split: 0.72 on average of 28 sizes (640 x 28672 at M = 48 21.9 -> 9.6 us); on
+// 12288 to 20480 columns they are even, on fewer the row groups are faster.
+bool wide_rows(int M, const tpdq_w4* w, int meta) {
   return meta == kMetaGroup && step_groups(w->group_size) && w->layout == TPDQ_LAYOUT_TILED && M > kTileM &&
-         M <= kDecodeMaxM && w->K >= 12288 && (int64_t)w->K * w->N >= ((int64_t)16 << 20);
+         M <= kDecodeMaxM && (int64_t)w->K * w->N >= ((int64_t)16 << 20) &&
+         (w->K >= 12288 || (M > 2 * kTileM && w->N >= 25600));
 }
 
 // Rows of one launch of the decode kernels (the last launch of a call may have
@@ -208,7 +212,7 @@ bool decode_plan_for(int mc, bool perm, const tpdq_w4* w, int meta, int dt, Deco
                      bool* prepared, bool gated, bool* plain, size_t avail, bool whole) {
   *prepared = false;
   if (plain) *plain = false;
-  if (!perm && !gated && whole && long_rows(mc, w, meta))
+  if (!perm && !gated && whole && wide_rows(mc, w, meta))
     return plan_decode(mc, w->K, w->N, w->group_size, w->num_groups, w->layout, meta, kOperandPlain, dt, plan,
                        false, true);
   const bool copy = meta == kMetaGroup && step_groups(w->group_size)

@@ -170,7 +170,7 @@ double rows_cost(int M, const tpdq_w4* w, bool prepared) {
 }
 
 bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int meta_pref, int operand,
-                 int dt, DecodePlan* p, bool gated, bool split_long) {
+                 int dt, DecodePlan* p, bool gated, bool wide_rows) {
   if (M < 1 || M > kRowsMaxM) return false;
   int mt = M <= 16 ? 1 : (M <= 32 ? 2 : 4);
   const int ntiles = (N + kTileN - 1) / kTileN;
@@ -264,9 +264,9 @@ bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int met
   // large (the decode kernel re-reads X for every 16 columns): 8 waves over
   // 128 columns share X through LDS, K split until about kWideTargetWgs
   // workgroups stream; more than 32 rows of X as it is are the M-tiled kernel's
-  // (on smaller weights, split_long: see long_rows)
+  // (on smaller weights, wide_rows: see abi.hip)
   p->wide = !gated && meta == kMetaGroup && layout == TPDQ_LAYOUT_TILED && a_global(am) &&
-            M <= kDecodeMaxM && (split_long || (!(mt == 4 && am == kAGlobal) && (int64_t)K * N >= kWideMinWeights));
+            M <= kDecodeMaxM && (wide_rows || (!(mt == 4 && am == kAGlobal) && (int64_t)K * N >= kWideMinWeights));
   p->rgs = 1;
   if (meta == kMetaGroup && a_global(am) && !p->wide && M > kTileM) {
     plan_rows(M, K, N, layout, spg, gated, operand == kOperandPrepared, &mt, &tn);

@@ -145,9 +145,9 @@ constexpr int kGatherOnceTiles = 512;
 // covers the request (for kOperandGather: the gather is not planned inside
 // the kernel, the caller then gathers X' first, row-major (launch_gather_plain,
 // planning with kOperandPlain) or in operand order (launch_gather_prep,
-// kOperandPrepared)). split_long: the wide kernel whatever the weight's size.
+// kOperandPrepared)). wide_rows: the wide kernel whatever the weight's size.
 bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int meta_pref, int operand,
-                 int dt, DecodePlan* p, bool gated = false, bool split_long = false);
+                 int dt, DecodePlan* p, bool gated = false, bool wide_rows = false);
 // the kernel of a plan, per element type (gemm_decode.hip, gemm_decode_bf16.hip)
 typedef void (*DecodeKernel)(GemmArgs);
 DecodeKernel decode_kernel_f16(const DecodePlan& p);

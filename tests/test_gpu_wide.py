@@ -1,5 +1,5 @@
 """GPU wide decode kernel (ordered path, tiled weights of at least 64M
-elements, or of 16M with row-major X, M > 16 and K >= 12288: X too large to
+elements, or of 16M with row-major X, M > 16 and K >= 12288 or N >= 25600: X too large to
 stage whole in LDS, 8 waves over 128 columns share the activations through LDS,
 K split over workgroups when the columns alone give too few) against the oracle on sampled columns."""
 import numpy as np
@@ -24,6 +24,8 @@ SHAPES = [
     # long rows of 16M to 64M elements: the wide kernel on row-major X, row groups
     # after a gather; ragged N, a partial last group and block
     (12288, 1544, 32, 64), (16392, 1032, 64, 33), (16384, 1160, 256, 17), (34816, 512, 128, 48),
+    # ... and many columns
+    (648, 28680, 128, 48), (1016, 25608, 32, 33),
 ]
 
 

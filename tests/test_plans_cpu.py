@@ -83,6 +83,15 @@ def test_short_rows_keep_their_pair(record):
         assert [mt for mt, _, _, _ in _ordered(r)] == [1]
 
 
+# ... and over many columns the row groups ran four rounds of one workgroup per CU
+# (640 x 28672 at M = 48, 9.6 -> 21.9 us)
+@pytest.mark.parametrize("K,N,G,M", [(640, 28672, 128, 48), (1016, 30480, 32, 33), (1536, 27136, 64, 64)])
+def test_many_columns_take_the_wide_kernel(record, K, N, G, M):
+    r, r17 = record([dict(op="gemm", M=m, K=K, N=N, G=G, gidx=False) for m in (M, 17)])
+    assert [l["kernel"].split("<")[0] for l in r["launches"]] == ["k_wide"] and launches.outside(r) == []
+    assert len(_ordered(r17)) == 1
+
+
 # exact tiles cost more the smaller the group
 @pytest.mark.parametrize("K,N,G,dtype,M,kernel", [
     (6144, 6144, 32, "bf16", 200, "k_prefill<1, 8, 2, 4"),    # row groups 80 us, 64-row tiles 49
