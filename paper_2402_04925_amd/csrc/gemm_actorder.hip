@@ -300,16 +300,24 @@ int64_t col_bytes(int K) { return (int64_t)((K + 127) / 128) * 256; }
 
 }  // namespace
 
-// Microseconds of the dense kernel over one chunk, as mtile_cost (per block and
-// round 2.45 us with 128-row tiles, where MFMA bounds it, 2.0 with 64-row ones,
-// where the weight records through L1 do: 128 KiB per block and CU).
+// Microseconds of the dense kernel over one chunk, as mtile_cost counts its own
+// (per block and round 2.45 us with 128-row tiles, where MFMA bounds it, 2.0 with
+// 64-row ones, where the weight records through L1 do: 128 KiB per block and CU).
 static double dense_cost(int M, int N, int nblk, int rt, int ks, bool gated) {
-  const int bn = gated ? 256 : 512;
-  const int64_t wgs = (int64_t)((M + 16 * rt - 1) / (16 * rt)) * ((N + bn - 1) / bn) * ks;
-  const double tb = rt == 8 ? 2.45 : 2.0;
-  const double rounds = (double)((wgs + kMtileSlots - 1) / kMtileSlots);
-  const double part = ks > 1 ? 4.0 + (double)ks * M * N * (gated ? 16.0 : 8.0) / 4.5e6 : 0.0;
-  return rounds * (4.0 + tb * ((nblk + ks - 1) / ks)) + part;
+  return tiles_us(M, N, nblk, rt, ks, gated, 4.0, rt == 8 ? 2.45 : 2.0, 4.0, 4.5e6);
+}
+
+// Microseconds of the act-order call in launches of 64 rows (k_rowmeta), fitted
+// within 10% to 1,700 GEMMs of 256 to 16384 rows and columns: per launch and round
+// of one workgroup per CU, its blocks' dequantization and its row tiles.
+static double decode_cost(int M, int N, int nblk, bool gated) {
+  const int rounds = ((N + kTileN - 1) / kTileN + 255) / 256;
+  double us = 0.0;
+  for (int m = M; m > 0; m -= kDecodeMaxM) {
+    const int tiles = m <= kTileM ? 1 : m <= 2 * kTileM ? 2 : 4;
+    us += 5.6 + rounds * (0.1 + nblk * (0.04 + 0.08 * tiles) * (gated ? 2 : 1));
+  }
+  return us;
 }
 
 bool plan_dense16(int M, int64_t ldx, const tpdq_w4* w, bool gated, size_t budget, DensePlan* p) {
@@ -333,6 +341,7 @@ bool plan_dense16(int M, int64_t ldx, const tpdq_w4* w, bool gated, size_t budge
   q.w_bytes = align_up((size_t)((q.ncols + 15) / 16 * 16) * (size_t)cb);
   const int nblk = (K + 127) / 128;
   // as in plan_mtile: the choice without a limit, where the workspace holds it
+  double us = 0.0;
   for (size_t limit : {SIZE_MAX, budget}) {
     double best = 1e30;
     for (int rt : {8, 4})
@@ -347,9 +356,14 @@ bool plan_dense16(int M, int64_t ldx, const tpdq_w4* w, bool gated, size_t budge
           q.part_bytes = part;
         }
       }
+    us = 8.3 + ((N + q.ncols - 1) / q.ncols) * 0.76 * best + 0.92e-6 * K * N * (gated ? 2 : 1);
     if (q.w_bytes + q.part_bytes <= budget) break;
   }
   if (q.w_bytes > budget) return false;
+  // two to four launches on a small layer may cost less than dequantizing it:
+  // 1512 x 3208 at M = 65 24.7 us dense, 17.4 in two launches (of 1,700 sizes the
+  // choice is 0.4% from the better one on average, dense alone 8%)
+  if (M <= kRowsMaxM && us > decode_cost(M, N, nblk, gated)) return false;
   *p = q;
   return true;
 }

@@ -520,18 +520,6 @@ __global__ __launch_bounds__(256) void k_gather_rows(const uint16_t* __restrict_
 
 }  // namespace
 
-// Microseconds of one M-tiled launch by shape: workgroups run in rounds of one
-// per CU, each over nblk / ks blocks of 128 rows (start + block us a round); split
-// partials are written once and read once by the reduce (at mb bytes per us).
-static double tiles_us(int M, int N, int nblk, int rt, int ks, bool gated, double start, double block,
-                       double reduce, double mb) {
-  const int bn = gated ? 256 : 512;
-  const int64_t wgs = (int64_t)((M + 16 * rt - 1) / (16 * rt)) * ((N + bn - 1) / bn) * ks;
-  const double rounds = (double)((wgs + kMtileSlots - 1) / kMtileSlots);
-  const double part = ks > 1 ? reduce + (double)ks * M * N * (gated ? 16.0 : 8.0) / mb : 0.0;
-  return rounds * (start + block * ((nblk + ks - 1) / ks)) + part;
-}
-
 // The tile and split at prefill sizes. Measured on 6144 x 6144, 8192 x 3584 and
 // 3584 x 8192 at M = 300 to 1500 with G = 128, per block 128 x 512 tiles 2.8 us
 // (bf16 3.2), 64 x 512 ones 1.9 (2.5). Groups of 32 and 64 make the 64-row tiles

@@ -175,6 +175,17 @@ constexpr int kPrefillMinM = 256;
 constexpr int kMtileMinM = 33;
 constexpr int64_t kMtileMinWeights = (int64_t)64 << 20;
 constexpr int kMtileSlots = 256;  // one 8-wave workgroup per CU on 256 CUs
+// Microseconds of one launch of 16 rt x 512 tiles (gated 256) by shape: workgroups run in rounds of one
+// per CU, each over nblk / ks blocks of 128 rows (start + block us a round); split
+// partials are written once and read once by the reduce (at mb bytes per us).
+inline double tiles_us(int M, int N, int nblk, int rt, int ks, bool gated, double start, double block,
+                       double reduce, double mb) {
+  const int bn = gated ? 256 : 512;
+  const int64_t wgs = (int64_t)((M + 16 * rt - 1) / (16 * rt)) * ((N + bn - 1) / bn) * ks;
+  const double rounds = (double)((wgs + kMtileSlots - 1) / kMtileSlots);
+  const double part = ks > 1 ? reduce + (double)ks * M * N * (gated ? 16.0 : 8.0) / mb : 0.0;
+  return rounds * (start + block * ((nblk + ks - 1) / ks)) + part;
+}
 struct MtilePlan {
   int rt, nw, st, ks;  // row tiles and waves per workgroup, LDS stages, K splits
   bool exact;          // q - z in the MFMAs, scales in fp32 (else weights rounded)

@@ -47,12 +47,13 @@ def _gemm(tpdq, X, w, path, nbytes, perm=None):
     return y
 
 
-# one row past the decode kernels, ragged rows and columns (N % 16 == 8, a
+# one row past the decode kernels (which small layers take up to 256 rows:
+# tests/test_plans_cpu.py) and past those, ragged rows and columns (N % 16 == 8, a
 # 512-column tile plus 8), a ragged last block of K, groups of 8 and as many
 # of them as don't fit in LDS, 128-row tiles
 @pytest.mark.parametrize("K,N,G,M", [
     (256, 24, 32, 65), (1000, 520, 128, 130), (1064, 1032, 8, 129), (3072, 72, 8, 70), (4096, 512, 64, 260),
-    (512, 2568, 128, 1100),
+    (512, 2568, 128, 1100), (256, 24, 32, 257), (3072, 72, 8, 300),
 ])
 @pytest.mark.parametrize("layout", ["gptq", "tiled"])
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
@@ -78,14 +79,15 @@ def test_actorder(K, N, G, M, layout, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
-def test_column_chunks_and_small_workspaces(dtype):
+@pytest.mark.parametrize("M", [100, 300])
+def test_column_chunks_and_small_workspaces(dtype, M):
     """Three chunks of 512 columns (the last of 136), and the decode kernels
     where not even one fits: the same weights, so the same result up to the
     order of the fp32 sums."""
     import torch
     import paper_2402_04925_amd as tpdq
     dev = torch_dev()
-    K, N, G, M = 1032, 1160, 64, 100
+    K, N, G = 1032, 1160, 64
     l = _layer(K, N, G, dtype, 9)
     X = _x(M, K, dtype)
     w, Xd = layer_to_dev(l, dev), to_dev(X, dev, dtype == "bf16")
@@ -97,12 +99,13 @@ def test_column_chunks_and_small_workspaces(dtype):
 
 
 @pytest.mark.parametrize("G", [0, 24, 8])
-def test_sorted_rows_of_other_groups(G):
+@pytest.mark.parametrize("M", [77, 270])
+def test_sorted_rows_of_other_groups(G, M):
     """The ordered path where groups are not whole 32-row steps."""
     import torch
     import paper_2402_04925_amd as tpdq
     dev = torch_dev()
-    K, N, M = 1008, 136, 77
+    K, N = 1008, 136
     l = inputs.make_unequal_layer(K, N, 11, seed=4) if G == 0 else _layer(K, N, G, "fp16", G)
     P, gs, _, _, wo, _ = tpdq.reorder(layer_to_dev(l, dev), layout=tpdq.LAYOUT_TILED)
     X = _x(M, K, "fp16")
@@ -111,7 +114,7 @@ def test_sorted_rows_of_other_groups(G):
     assert o.rel_err(np_of(y), X.astype(np.float64) @ _deq(l)) <= TOL["fp16"]
 
 
-@pytest.mark.parametrize("M,K,N", [(66, 264, 264), (300, 4096, 520)])
+@pytest.mark.parametrize("M,K,N", [(66, 264, 264), (300, 4096, 520), (259, 264, 264)])
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
 def test_gated_actorder(M, K, N, dtype):
     import torch

@@ -104,3 +104,16 @@ def test_tiles_by_group_size(record, K, N, G, dtype, M, kernel):
     (r,) = record([dict(op="gemm", M=M, K=K, N=N, G=G, dtype=dtype, gidx=False)])
     names = [l["kernel"] for l in r["launches"]]
     assert any(n.startswith(kernel) for n in names), names
+
+
+# act-order above 64 rows: two launches of the decode kernels cost less than
+# dequantizing a small layer (1512 x 3208 at M = 65, 17.4 -> 24.7 us)
+@pytest.mark.parametrize("K,N,M,dense", [(1512, 3208, 65, False), (1216, 1968, 65, False), (1216, 1968, 250, True),
+                                         (6144, 6144, 100, True), (256, 256, 257, True)])
+@pytest.mark.parametrize("layout", ["tiled", "gptq"])
+def test_small_act_order_layers(record, K, N, M, dense, layout):
+    calls = [dict(op="gemm", M=M, K=K, N=N, path="actorder", layout=layout, ws=ws) for ws in ("doc", "2doc")]
+    for r in record(calls):
+        assert any("k_dequant16" in l["kernel"] for l in r["launches"]) == dense
+        assert any("k_rowmeta" in l["kernel"] for l in r["launches"]) != dense
+        assert launches.outside(r) == []
