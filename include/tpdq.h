@@ -241,15 +241,16 @@ tpdq_status tpdq_mlp_shard(const void* X, int64_t ldx, int32_t M, const int32_t*
 /*
  * tpdq_mlp_shard_noalloc - tpdq_mlp_shard for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops, harnesses
- * that forbid hipMalloc): the same computation, kernels and results, without a
- * workspace argument. The workspace is a static scratch array of 64 MiB that
+ * that forbid hipMalloc): the same computation without a workspace argument,
+ * through the kernels that a 64 MiB workspace allows (the same as a caller's
+ * workspace of the documented size gives where that is 64 MiB or less). The workspace is a static scratch array of 64 MiB that
  * the library holds on each GPU it runs on until the process ends; this call
  * never allocates or frees device memory and calls no allocating routine.
  * Arguments, alignment and results as for tpdq_mlp_shard; the scratch serves
- * the stream's device. A call whose tpdq_workspace_bytes(2, M, w1, w2) exceeds
- * 64 MiB returns TPDQ_ERR_WORKSPACE before any device work (every decode and
- * prefill shape of the paper's workloads fits; e.g. M = 2048 on the Llama-70B
- * TP = 2 shard uses 32 MiB). The scratch needs no particular content. All
+ * the stream's device. A call whose slowest route, the one with the least
+ * workspace, takes more than 64 MiB returns TPDQ_ERR_WORKSPACE before any device
+ * work (every decode and prefill shape of the paper's workloads fits; e.g. M =
+ * 2048 on the Llama-70B TP = 2 shard uses 32 MiB). The scratch needs no particular content. All
  * calls on one GPU share its scratch: calls that overlap in time on one GPU
  * (two streams, two threads) race and must be serialised by the caller. The
  * first call on a device resolves that device's scratch address (a runtime
@@ -279,9 +280,13 @@ tpdq_status tpdq_mlp_shard_noalloc(const void* X, int64_t ldx, int32_t M, const 
  * w_up must have w_gate's K, N, group size, num_groups, layout, leading
  * dimensions and zero offset (TPDQ_ERR_SHAPE otherwise); w_down->K == w_gate->N.
  * X, Y1, Y2_partial, alignment and workspace as for tpdq_mlp_shard, with
- * tpdq_workspace_bytes(3, M, w_gate, w_down). On the ordered path with tiled
- * weights, M > 64 runs the M-tiled kernel (64-row tiles, weights kept exact);
- * every other call the decode kernels (more than 64 rows in launches of 64).
+ * tpdq_workspace_bytes(3, M, w_gate, w_down). Above 64 rows the gate and up GEMM
+ * runs, where the workspace holds what it takes, the M-tiled kernel on the ordered
+ * path with tiled weights (64-row tiles, weights kept exact), launches of up to 256
+ * rows with GPTQ-layout ones (exact), and on TPDQ_PATH_ACTORDER a dense kernel on
+ * weights dequantized once (rounded to the element type, as every act-order kernel
+ * rounds them) unless the layer is small; every other call the decode kernels in
+ * launches of 64 rows.
  */
 tpdq_status tpdq_gated_mlp_shard(const void* X, int64_t ldx, int32_t M, const int32_t* P1,
                                  const tpdq_w4* w_gate, const tpdq_w4* w_up, const tpdq_w4* w_down,

@@ -94,8 +94,8 @@ tpdq_status check_layer(const tpdq_w4* w, const char* name, bool need_gidx, bool
 // Workspace of one GEMM call. The decode kernels use it only for the
 // gathered activations when the gather X[:, perm] cannot be done inside the
 // GEMM's LDS: the prepared operand (k_gather_prep: 16 rows x 128 columns x
-// 2 bytes per row tile and 128-row block, chunks of 64 rows). The M-tiled
-// kernel uses [X[:, perm] row-major, M x K x 2 bytes, when perm is given]
+// 2 bytes per row tile and 128-row block, launches of 64 or, in row groups, 256
+// rows). The M-tiled kernel uses [X[:, perm] row-major, M x K x 2 bytes, when perm is given]
 // [fp32 split-K partials].
 size_t prepared_bytes(int rows, int K) {
   return align_up((size_t)((rows + kTileM - 1) / kTileM) * ((K + 127) / 128) * 4096);
@@ -194,7 +194,7 @@ bool dense_for(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, bool g
   return avail > *gather && plan_dense16(M, perm ? (int64_t)w->K : ldx, w, gated, avail - *gather, p);
 }
 
-// The decode plan of one launch of mc <= 64 rows, as run_gemm makes it: with
+// The decode plan of one launch of mc rows, as run_gemm makes it: with
 // a perm, the gather inside the kernel's LDS if it is planned; else, up to 4
 // rows, X' gathered once row-major when the tile kernel then takes it like
 // any X (*plain); else the prepared operand (*prepared). The workspace of the
@@ -301,7 +301,7 @@ int meta_mode(tpdq_path path) {
 }
 
 // Extra inputs and outputs of one GEMM inside the MLP (decode kernels, one
-// launch of M <= 64 rows): yp receives a second copy of Y in the prepared
+// launch, mlp_prepared_y1): yp receives a second copy of Y in the prepared
 // operand layout of the next GEMM; x_prepared says X already is one.
 struct GemmIO {
   uint16_t* yp = nullptr;
@@ -310,8 +310,8 @@ struct GemmIO {
   const tpdq_w4* up = nullptr;  // gated GEMM: Y = silu(X' W) * (X' W_up)
 };
 
-// One GEMM: the M-tiled kernel where it is planned (ws holds ws_bytes), else
-// the decode kernels, M cut into launches of <= 64 rows.
+// One GEMM: the M-tiled or the dequantize-once kernels where they are planned (ws
+// holds ws_bytes), else the decode kernels, M cut into launches of chunk_rows.
 // perm != NULL: the operand is X[:, perm]; it is gathered inside the kernel
 // when it fits in LDS, else into the workspace first (already in operand
 // order).

@@ -1,4 +1,5 @@
-// Planning and launch of the decode GEMMs (M <= 64), and the gather of the
+// Planning and launch of the decode GEMMs (launches of up to 64 rows, row groups
+// of the ordered kernel up to 256), and the gather of the
 // activations into decode operand order. The kernels are in decode_kernels.h;
 // this file instantiates them for fp16, gemm_decode_bf16.hip for bf16.
 #include "decode_kernels.h"
@@ -10,11 +11,6 @@
 namespace tpdq {
 namespace {
 
-// The prepared operand: X'[m][k] = X[m][perm[k]] (perm NULL: X itself) as
-// 16-byte records [row tile t][step s][lane l]: row 16 t + l % 16, operand
-// rows 8 (4 s + l / 16) .. +7 in operand order (natural for tiled weights,
-// x0, x4, x1, x5, ... for GPTQ ones), zero past M or K. A decode wave reads one step of one row tile as one
-// contiguous KiB.
 // X'[m][k] = X[m][perm[k]] row-major [M][K], one octet per thread: for a
 // decode GEMM that then stages X' in LDS (or reads it row-major) like any X.
 __global__ __launch_bounds__(64) void k_gather_plain(const uint16_t* __restrict__ X, int64_t ldx,
@@ -41,6 +37,11 @@ __global__ __launch_bounds__(64) void k_gather_plain(const uint16_t* __restrict_
   }
 }
 
+// The prepared operand: X'[m][k] = X[m][perm[k]] (perm NULL: X itself) as
+// 16-byte records [row tile t][step s][lane l]: row 16 t + l % 16, operand
+// rows 8 (4 s + l / 16) .. +7 in operand order (natural for tiled weights,
+// x0, x4, x1, x5, ... for GPTQ ones), zero past M or K. A decode wave reads one
+// step of one row tile as one contiguous KiB.
 __global__ __launch_bounds__(64) void k_gather_prep(const uint16_t* __restrict__ X, int64_t ldx,
                                                     int M, int K, const int32_t* __restrict__ perm,
                                                     int natural, uint16_t* __restrict__ Xp) {
