@@ -27,10 +27,12 @@
 // error 2^-12). With bf16 activations the weight is formed in fp32 and rounded
 // once to bf16 (relative error 2^-9), about four times the VALU work of fp16.
 // Most 64-row tiles (EXACT, see k_prefill) keep q - z in the MFMAs and scale in
-// fp32 as the decode kernels do, which costs them nothing (6144 x 6144 at M =
-// 512: 94.5 us, rounded 88.7 us; bf16 faster than rounded): they also serve
-// what would otherwise run in decode launches of 64 rows. Gated Llama-70B TP=8 MLP at M = 1000,
-// bf16: 514 -> 222 us (gate and up in one launch at 0.9 PFLOP/s).
+// fp32 as the decode kernels do, for 6% more time than rounded weights in fp16 (6144
+// x 6144, G = 128, M = 512, no K split: 94.5 us against 88.7; bf16 is faster than
+// rounded; groups of 64 and 32 cost 25 and 55% more per block than G = 128): they
+// also serve what would otherwise run in decode launches of 64 rows. Gated
+// Llama-70B TP=8 MLP at M = 1000, bf16: 514 -> 220 us (gate and up in one launch
+// at 0.9 PFLOP/s).
 #include "kernels_common.h"
 
 #include <algorithm>
@@ -130,12 +132,11 @@ __device__ __forceinline__ void round_not_finite(const GemmArgs& a, uint64_t aga
   }
 }
 
-// RT row tiles (16 RT rows of Y per workgroup), NW waves (64 columns each),
-// ST stages (2 or 3) of LDS. With a.ks > 1 the workgroup covers one of ks
+// RT row tiles (16 RT rows of Y per workgroup), NW waves (64 columns each). With a.ks > 1 the workgroup covers one of ks
 // contiguous ranges of 128-row blocks of K and writes its fp32 partial tile
 // to a.part[split][M][N] (k_splitk_reduce sums the splits); else it writes
 // fp16 Y.
-// Two waves per SIMD (the 8-wave workgroup, or two 4-wave workgroups per CU):
+// Two waves per SIMD (the 8-wave workgroup):
 // 256 registers per lane, with the accumulators in the architectural VGPRs
 // (no accumulator copies between loop iterations).
 //
@@ -150,7 +151,7 @@ __device__ __forceinline__ void round_not_finite(const GemmArgs& a, uint64_t aga
 // columns of gate (tiles 0, 1) and the same 32 of up (tiles 2, 3), so that the
 // epilogue has both products of an element in one lane; split partials are
 // [split][gate, up][M][N].
-template <int SPG, int NW, int ST, int RT, int DT, bool EXACT = false, bool GATED = false>
+template <int SPG, int NW, int RT, int DT, bool EXACT = false, bool GATED = false>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_prefill(GemmArgs a) {
   static_assert(!EXACT || RT <= 4, "two accumulators per output");
   static_assert(!GATED || EXACT, "the gated product keeps its weights exact");
@@ -385,25 +386,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     }
   };
 
-  // Before block b: this wave's loads of block b have landed (with three
-  // stages, those of block b + 1 may still be in flight) and its LDS reads of
-  // block b - 1 are done; the barrier then publishes every wave's block b
-  // and frees the stage that receives the next block.
-  auto sync = [&]() {
-    if constexpr (ST == 3)
-      asm volatile("s_waitcnt vmcnt(%0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::"n"(LPB) : "memory");
-    else
-      asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  };
-#pragma unroll
-  for (int p = 0; p < ST - 1; ++p) issue(kb0 + p, p);
+  issue(kb0, 0);
   int st = 0;
 #pragma unroll 1
   for (int b = kb0; b < kb1; ++b) {
-    sync();
-    const int sn = st == 0 ? ST - 1 : st - 1;
-    compute(b, st, b + ST - 1, sn);
-    st = st == ST - 1 ? 0 : st + 1;
+    // this wave's loads of block b have landed and its LDS reads of block b - 1
+    // are done; the barrier then publishes every wave's block b and frees the
+    // stage that receives the next block
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    compute(b, st, b + 1, st == 0 ? 1 : st - 1);
+    st = st == 1 ? 0 : st + 1;
   }
   // the loads past the last block (zeros) still write LDS: let them land
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -561,8 +553,6 @@ bool plan_mtile(int M, int64_t ldx, const tpdq_w4* w, int meta, int dt, bool gat
         (int64_t)w->num_groups * w->ld_s * 2 < lim && (int64_t)w->num_groups * w->ld_z * 4 < lim))
     return false;
   MtilePlan q{};
-  q.nw = 8;
-  q.st = 2;
   q.ks = 1;
   q.gated = gated;
   const int nblk = (K + 127) / 128;
@@ -654,25 +644,23 @@ hipError_t launch_mtile_k(void (*k)(GemmArgs), int rt, bool gated, const GemmArg
 
 template <int RT, int DT, bool EXACT, bool GATED>
 hipError_t launch_mtile_t(const GemmArgs& a, int ks, hipStream_t s) {
-  constexpr int NW = 8, ST = 2;
   typedef void (*Kern)(GemmArgs);
   Kern k = nullptr;
   switch (a.G / 32) {
-    case 1: k = k_prefill<1, NW, ST, RT, DT, EXACT, GATED>; break;
-    case 2: k = k_prefill<2, NW, ST, RT, DT, EXACT, GATED>; break;
-    case 4: k = k_prefill<4, NW, ST, RT, DT, EXACT, GATED>; break;
-    case 8: k = k_prefill<8, NW, ST, RT, DT, EXACT, GATED>; break;
+    case 1: k = k_prefill<1, 8, RT, DT, EXACT, GATED>; break;
+    case 2: k = k_prefill<2, 8, RT, DT, EXACT, GATED>; break;
+    case 4: k = k_prefill<4, 8, RT, DT, EXACT, GATED>; break;
+    case 8: k = k_prefill<8, 8, RT, DT, EXACT, GATED>; break;
   }
   return k ? launch_mtile_k(k, RT, GATED, a, ks, s) : hipErrorInvalidValue;
 }
 
 template <int DT>
 hipError_t launch_mtile_dt(const GemmArgs& a, const MtilePlan& p, hipStream_t s) {
-  if (p.nw != 8 || p.st != 2) return hipErrorInvalidValue;
   if (p.rt == 4 && !p.exact) {  // groups of 32 and 64 only (plan_mtile)
     if (p.gated) return hipErrorInvalidValue;
-    if (a.G == 32) return launch_mtile_k(k_prefill<1, 8, 2, 4, DT, false, false>, 4, false, a, p.ks, s);
-    return a.G == 64 ? launch_mtile_k(k_prefill<2, 8, 2, 4, DT, false, false>, 4, false, a, p.ks, s)
+    if (a.G == 32) return launch_mtile_k(k_prefill<1, 8, 4, DT, false, false>, 4, false, a, p.ks, s);
+    return a.G == 64 ? launch_mtile_k(k_prefill<2, 8, 4, DT, false, false>, 4, false, a, p.ks, s)
                      : hipErrorInvalidValue;
   }
   if (p.rt == 4)

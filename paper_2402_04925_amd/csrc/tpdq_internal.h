@@ -15,9 +15,9 @@ namespace tpdq {
 constexpr size_t kWsAlign = 256;
 inline size_t align_up(size_t x, size_t a = kWsAlign) { return (x + a - 1) / a * a; }
 
-// Decode GEMM geometry: a workgroup owns 16 output columns over the whole K
+// Decode GEMM geometry: a workgroup owns 16 to 64 output columns over the whole K
 // range (no cross-workgroup reduction); its waves split K; one MFMA tile has
-// 16 rows of M; one launch handles up to 4 row tiles.
+// 16 rows of M, a workgroup up to 4 row tiles.
 constexpr int kTileN = 16;
 constexpr int kTileM = 16;
 constexpr int kDecodeMaxM = 64;
@@ -163,14 +163,16 @@ hipError_t launch_gather_plain(const uint16_t* X, int64_t ldx, int M, int K, con
 hipError_t launch_gather_prep(const uint16_t* X, int64_t ldx, int M, int K, const int32_t* perm,
                               int layout, uint16_t* Xp, hipStream_t s);
 
-// M-tiled MFMA GEMM (gemm_prefill.hip): sorted rows, tiled weights. At
-// M >= kPrefillMinM, 128 x 512 tiles over the whole K; from kMtileMinM rows,
-// on weights of at least kMtileMinWeights elements, 64 x 512 tiles with K
-// split over ks workgroups (fp32 partials in the workspace, summed in split
-// order by a second kernel). Below kMtileMinM rows the decode kernels are
-// faster (measured on the Llama-70B TP=1 shapes: at M = 16 the decode GEMMs
-// take 38 / 34 us, the split-K tiles 57 / 61 us; at M = 64, 127 / 111 us
-// against 70 / 64 us).
+// M-tiled MFMA GEMM (gemm_prefill.hip): sorted rows, tiled weights. From
+// kPrefillMinM rows on, 128 x 512 or 64 x 512 tiles over the whole K or a part of
+// it (fp32 partials in the workspace, summed in split order by a second kernel),
+// whichever costs less. From kMtileMinM rows on weights of at least
+// kMtileMinWeights elements 64 x 512 tiles (128 x 512 above 64 rows where they
+// cost less), K split over the CUs; from 65 rows on smaller weights, and for the
+// gated product, exact 64-row tiles where they cost less than the row groups.
+// Below kMtileMinM rows the decode kernels are faster (measured on the Llama-70B
+// TP=1 shapes: at M = 16 the decode GEMMs take 38 / 34 us, the split-K tiles 57 /
+// 61 us; at M = 64, 127 / 111 us against 70 / 64 us).
 constexpr int kPrefillMinM = 256;
 constexpr int kMtileMinM = 33;
 constexpr int64_t kMtileMinWeights = (int64_t)64 << 20;
@@ -187,7 +189,7 @@ inline double tiles_us(int M, int N, int nblk, int rt, int ks, bool gated, doubl
   return rounds * (start + block * ((nblk + ks - 1) / ks)) + part;
 }
 struct MtilePlan {
-  int rt, nw, st, ks;  // row tiles and waves per workgroup, LDS stages, K splits
+  int rt, ks;          // row tiles per workgroup, K splits
   bool exact;          // q - z in the MFMAs, scales in fp32 (else weights rounded)
   bool gated;          // Y = silu(X W) * (X W_up)
   double cost;         // exact plans: microseconds by the planner's model

@@ -94,11 +94,11 @@ def test_many_columns_take_the_wide_kernel(record, K, N, G, M):
 
 # exact tiles cost more the smaller the group
 @pytest.mark.parametrize("K,N,G,dtype,M,kernel", [
-    (6144, 6144, 32, "bf16", 200, "k_prefill<1, 8, 2, 4"),    # row groups 80 us, 64-row tiles 49
-    (3584, 8192, 64, "fp16", 200, "k_prefill<2, 8, 2, 4"),    # 47, 32
+    (6144, 6144, 32, "bf16", 200, "k_prefill<1, 8, 4"),    # row groups 80 us, 64-row tiles 49
+    (3584, 8192, 64, "fp16", 200, "k_prefill<2, 8, 4"),    # 47, 32
     (6144, 6144, 128, "fp16", 100, "k_ordered"),              # 22, 27
-    (53248, 2048, 64, "fp16", 160, "k_prefill<2, 8, 2, 4"),   # 128-row tiles 79, 64-row ones 68
-    (8192, 28672, 128, "fp16", 128, "k_prefill<4, 8, 2, 8"),  # 77, 85
+    (53248, 2048, 64, "fp16", 160, "k_prefill<2, 8, 4"),   # 128-row tiles 79, 64-row ones 68
+    (8192, 28672, 128, "fp16", 128, "k_prefill<4, 8, 8"),  # 77, 85
 ])
 def test_tiles_by_group_size(record, K, N, G, dtype, M, kernel):
     (r,) = record([dict(op="gemm", M=M, K=K, N=N, G=G, dtype=dtype, gidx=False)])
