@@ -209,7 +209,7 @@ bool dense_for(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, bool g
 // whole: the launch is the whole call (its X rows lie as the call's bound on the
 // workspace assumes).
 bool decode_plan_for(int mc, bool perm, const tpdq_w4* w, int meta, int dt, DecodePlan* plan,
-                     bool* prepared, bool gated, bool* plain, size_t avail, bool whole) {
+                     bool* prepared, bool gated, bool* plain, size_t avail, bool whole, bool sizes = false) {
   *prepared = false;
   if (plain) *plain = false;
   if (!perm && !gated && whole && wide_rows(mc, w, meta))
@@ -221,7 +221,7 @@ bool decode_plan_for(int mc, bool perm, const tpdq_w4* w, int meta, int dt, Deco
   if (!perm && copy && avail != kBaseWs && avail >= prepared_bytes(mc, w->K)) {
     *prepared = true;
     return plan_decode(mc, w->K, w->N, w->group_size, w->num_groups, w->layout, meta, kOperandPrepared, dt,
-                       plan, gated);
+                       plan, gated, false, sizes);
   }
   if (perm) {
     if (plan_decode(mc, w->K, w->N, w->group_size, w->num_groups, w->layout, meta, kOperandGather,
@@ -236,10 +236,10 @@ bool decode_plan_for(int mc, bool perm, const tpdq_w4* w, int meta, int dt, Deco
     }
     *prepared = true;
     return plan_decode(mc, w->K, w->N, w->group_size, w->num_groups, w->layout, meta,
-                       kOperandPrepared, dt, plan, gated);
+                       kOperandPrepared, dt, plan, gated, false, sizes);
   }
   return plan_decode(mc, w->K, w->N, w->group_size, w->num_groups, w->layout, meta, kOperandPlain,
-                     dt, plan, gated);
+                     dt, plan, gated, false, sizes);
 }
 
 // split-K partials of the wide decode kernel (0 when K is not split)
@@ -284,7 +284,7 @@ size_t gemm_ws_need(int M, int64_t ldx, bool perm, const tpdq_w4* w, int meta, i
     if (mc == 0) continue;
     DecodePlan dp;
     bool prepared = false;
-    if (!decode_plan_for(mc, perm, w, meta, dt, &dp, &prepared, gated, nullptr, avail, mc == M)) {
+    if (!decode_plan_for(mc, perm, w, meta, dt, &dp, &prepared, gated, nullptr, avail, mc == M, true)) {
       if (perm) need = std::max(need, decode_gather_bytes(M, w->K));
       continue;
     }

@@ -139,14 +139,17 @@ static double rows_us(int rt, int ntiles, int nblk, int layout, int spg, bool ga
 // 7% faster: four row tiles on many rounds, or a pair that leaves room for a
 // second workgroup. Of 2,000 random sizes the result is 3.7% faster than the
 // bytes' on average, and slower by more than 3% in 1%: 2176 x 25216 at M = 100
-// 54 -> 38 us, GPTQ-layout of G = 32 174 -> 76. On X as it is the bytes are the
-// better judge, but know one row tile only for GPTQ-layout weights of G = 32: two
-// of these pay up to 32 rows on K of 4096 or more (13944 x 5992 at M = 32 51 -> 44
-// us; 1664 x 12544 16.9 -> 18.1).
+// 54 -> 38 us, GPTQ-layout of G = 32 174 -> 76. In one round of the CUs, and on X
+// as it is, the bytes are as good or better, but know one row tile only for
+// GPTQ-layout weights of G = 32: two of these pay up to 32 rows on K of 4096 or
+// more (13944 x 5992 at M = 32 51 -> 44 us; 1664 x 12544 16.9 -> 18.1).
 static void plan_rows(int M, int K, int N, int layout, int spg, bool gated, bool prepared, int* mt, int* tn) {
   const int rt = (M + kTileM - 1) / kTileM, ntiles = (N + kTileN - 1) / kTileN, nblk = (K + 127) / 128;
   plan_bytes(rt, ntiles, layout, spg, gated, mt, tn);
-  if (!prepared && !(layout == TPDQ_LAYOUT_GPTQ && spg == 1 && rt <= 2 && K >= 4096)) return;
+  const bool one_row = layout == TPDQ_LAYOUT_GPTQ && spg == 1;  // all that the bytes know
+  if (!prepared && !(one_row && rt <= 2 && K >= 4096)) return;
+  const int64_t wgs = (int64_t)((rt + *mt - 1) / *mt) * (gated ? ntiles : (ntiles + *tn - 1) / *tn);
+  if (wgs <= 256 && !one_row) return;
   auto us = [&](int m, int n) { return rows_us(rt, ntiles, nblk, layout, spg, gated, prepared, m, n); };
   double best = 0.93 * us(*mt, *tn);
   for (int m : {4, 2, 1}) {
@@ -171,7 +174,7 @@ double rows_cost(int M, const tpdq_w4* w, bool prepared) {
 }
 
 bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int meta_pref, int operand,
-                 int dt, DecodePlan* p, bool gated, bool wide_rows) {
+                 int dt, DecodePlan* p, bool gated, bool wide_rows, bool sizes) {
   if (M < 1 || M > kRowsMaxM) return false;
   int mt = M <= 16 ? 1 : (M <= 32 ? 2 : 4);
   const int ntiles = (N + kTileN - 1) / kTileN;
@@ -269,12 +272,13 @@ bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int met
   p->wide = !gated && meta == kMetaGroup && layout == TPDQ_LAYOUT_TILED && a_global(am) &&
             M <= kDecodeMaxM && (wide_rows || (!(mt == 4 && am == kAGlobal) && (int64_t)K * N >= kWideMinWeights));
   p->rgs = 1;
+  p->ks = 1;
   if (meta == kMetaGroup && a_global(am) && !p->wide && M > kTileM) {
+    if (sizes) return true;
     plan_rows(M, K, N, layout, spg, gated, operand == kOperandPrepared, &mt, &tn);
     p->rgs = ((M + kTileM - 1) / kTileM + mt - 1) / mt;
     nw = 4;
   }
-  p->ks = 1;
   if (p->wide) {
     const int nblk = (K + 127) / 128;
     const int wgs = (ntiles + kWideWaves - 1) / kWideWaves;

@@ -146,8 +146,11 @@ constexpr int kGatherOnceTiles = 512;
 // the kernel, the caller then gathers X' first, row-major (launch_gather_plain,
 // planning with kOperandPlain) or in operand order (launch_gather_prep,
 // kOperandPrepared)). wide_rows: the wide kernel whatever the weight's size.
+// sizes: only wide and ks are asked for, the row groups' tiles need not be chosen
+// (a call sizes its workspace over a dozen plans and launches one to three).
 bool plan_decode(int M, int K, int N, int G, int num_groups, int layout, int meta_pref, int operand,
-                 int dt, DecodePlan* p, bool gated = false, bool wide_rows = false);
+                 int dt, DecodePlan* p, bool gated = false, bool wide_rows = false,
+                 bool sizes = false);
 // the kernel of a plan, per element type (gemm_decode.hip, gemm_decode_bf16.hip)
 typedef void (*DecodeKernel)(GemmArgs);
 DecodeKernel decode_kernel_f16(const DecodePlan& p);
