@@ -615,8 +615,8 @@ struct ChunkMeta {
 // workgroup owns TN 16-column tiles and one of a.rgs groups of MT row tiles
 // over all of K. With X read from global memory the bytes per CU bound it: per
 // 128 rows of K a workgroup reads 4 MT KiB of activations from L2 and TN KiB
-// of weights, so more than 16 rows of M are cut into row groups of one or two
-// tiles with up to four column tiles (see plan_rows), neighbouring workgroups
+// of weights, so more than 16 rows of M are cut into row groups of one, two or
+// four tiles with up to four column tiles (see plan_rows), neighbouring workgroups
 // sharing their weights in L2. M = 64 with the gather of X before it, one
 // workgroup with all four row tiles and at most two column tiles against row
 // groups: 6144 x 6144 23.6 -> 16.9 us, 8192 x 3584 24.7 -> 16.9, 3584 x 8192
